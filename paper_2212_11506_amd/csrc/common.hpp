@@ -29,8 +29,9 @@ constexpr int kBBoxBlocks = 512;
 // at most kEvalMaxBlocks blocks striding over the rows
 constexpr int kZEvalPoints = 2048;
 constexpr int kEvalMaxBlocks = 2048;
-// repulsive walk: 16 waves of consecutive points per block share one CU, so
-// their walks, which overlap in most nodes, share the scalar cache's lines
+// repulsive walk: the waves of consecutive points in a block (16 at most) share
+// one CU, so their walks, which overlap in most nodes, share the scalar cache's
+// lines
 constexpr int kRepBlock = 1024;
 // A node of the pre-order tree: one 24-byte record
 //   {com.x, com.y, count, thr, next, self}
@@ -123,18 +124,14 @@ struct Header {
 };
 
 struct Layout {
-    int64_t n, nnz, sort_tiles, scan_tiles, rep_blocks;
+    int64_t n, nnz, sort_tiles, scan_tiles;
     size_t header, hist, bbox_part, codes0, codes1, idx0, idx1, status, ycopy, ys, levelmask,
-        split_b, split_e, base, psum, scan_cnt, scan_sum, nodes, frep, fattr, partial, zpart, ipart, eval_part, total;
+        split_b, split_e, base, psum, scan_cnt, scan_sum, nodes, frep, fattr, partial, eval_part, total;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-inline int64_t rep_blocks_for(int64_t n)
-{
-    int64_t b = (n + kRepBlock - 1) / kRepBlock;
-    return (b + 7) / 8 * 8; // multiple of 8 for the XCD-contiguous remap
-}
+inline int64_t spare_for(int64_t n) { return ((n + 1023) / 1024 + 7) / 8 * 8; }
 
 // `fbytes` is the size of a coordinate: 4 (fp32 path) or 8 (fp64 variant,
 // which sizes the copies of Y, the node records and F_rep for fp64); `dim`
@@ -146,7 +143,6 @@ inline Layout make_layout(int64_t n, int64_t nnz, int fbytes = 4, int dim = 2)
     L.nnz = nnz;
     L.sort_tiles = (n + kSortTile - 1) / kSortTile;
     L.scan_tiles = (n + 1 + kScanTile - 1) / kScanTile;
-    L.rep_blocks = rep_blocks_for(n);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -179,10 +175,11 @@ inline Layout make_layout(int64_t n, int64_t nnz, int fbytes = 4, int dim = 2)
     // tiles of kTileRows rows per row block
     L.partial = take(size_t(dim) * size_t(fbytes) * size_t((n + kTileRows - 1) / kTileRows) * kTileRows *
                      size_t(kTileSlots));
-    L.zpart = take(8 * size_t(L.rep_blocks));
+    // (no longer used: the total is what callers sized, and bhtsne_step_noalloc's limit)
+    take(8 * size_t(spare_for(n)));
     const int64_t zb = (n + kZEvalPoints - 1) / kZEvalPoints;
     L.eval_part = take(8 * size_t(zb > kEvalMaxBlocks ? zb : kEvalMaxBlocks));
-    L.ipart = take(8 * size_t(L.rep_blocks));
+    take(8 * size_t(spare_for(n)));
     L.total = off;
     return L;
 }

@@ -19,6 +19,8 @@
 #include "common.hpp"
 #include "kernels.hpp"
 
+#include <algorithm>
+
 namespace bht {
 
 __device__ inline float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -70,15 +72,32 @@ __device__ inline void take_node(uint64_t take, float d2, float dx, float dy, fl
 // its own leaf and takes it once with d2 = 0: a weight of exactly 1 in z and
 // nothing in the force, removed after the walk.  Larger theta compares the
 // leaf's position with the lane's.
-template <bool kSelf>
-__device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi, uint32_t si, uint32_t &resume,
-                                      float &fx, float &fy, float &z, uint32_t &inter)
+//
+// A visit is a chain: the record's scalar load, the compares, the choice of the
+// next record.  The next record is loaded as soon as it is chosen, before the
+// accumulation of the one in hand, which takes as long as the compares; two
+// visits a round alternate between two sets of registers, so nothing is moved.
+// The load past the last record stays inside the array's padding.  (Walks that
+// several waves share, fp64 and 3-D: fp64 400k points 451 -> 424 us, 3-D 150k 718
+// -> 622.  With 8 waves a SIMD the 2-D fp32 walk is bound by issue and its
+// simpler loop is as fast: 1M points 447 us against 455.)
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+
+// The words of a record that a visit does not read count as read when it
+// starts: their registers would be given to other values while the load that
+// fills them is in flight, and the wave would wait for it there.  After the
+// loop they keep its last load from being moved behind the exit test.
+__device__ inline void keep_loaded(const u32x8 &r) { asm volatile("" ::"s"(r[5]), "s"(r[6]), "s"(r[7])); }
+
+template <bool kSelf, bool kAhead>
+__device__ inline void repulsive_walk(const char *nbase, uint32_t cur, uint32_t end, float2 yi, uint32_t si,
+                                      uint32_t &resume, float &fx, float &fy, float &z, uint32_t &inter)
 {
-    uint32_t cur = 0; // byte offset of the current record
-    while (cur < end) {
-        // the record and 8 bytes beyond it: one 32-byte scalar load
-        typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-        const u32x8 r = *reinterpret_cast<const u32x8 *>(nbase + cur);
+    if (cur >= end) return; // cur: byte offset of the current record
+    // the record and 8 bytes beyond it: one 32-byte scalar load
+    auto load = [&](uint32_t at) { return *reinterpret_cast<const u32x8 *>(nbase + at); };
+    auto visit = [&](const u32x8 &r, u32x8 &after) {
+        if (kAhead) keep_loaded(r);
         const float cx = __uint_as_float(r[0]), cy = __uint_as_float(r[1]);
         const float cnt = __uint_as_float(r[2]), thr = __uint_as_float(r[3]);
         const uint32_t next = r[4];
@@ -87,12 +106,27 @@ __device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi
         const uint64_t act = mask_uge(cur, resume);
         uint64_t take = act & mask_ogt(d2, thr);
         if (kSelf) take &= mask_ne(r[5], si);
-        const uint64_t rej = act & ~take;
+        // the first child follows its cell; no lane descends: jump past the subtree
+        cur = take != act ? cur + kNodeBytes : next;
+        if (kAhead) {
+            after = load(cur);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         inter += uint32_t(__builtin_popcountll(take));
         take_node(take, d2, dx, dy, cnt, next, z, fx, fy, resume);
-        // the first child follows its cell; no lane descends: jump past the subtree
-        cur = rej ? cur + kNodeBytes : next;
+        return cur < end;
+    };
+    if (!kAhead) {
+        u32x8 none;
+        while (visit(load(cur), none)) {
+        }
+        return;
     }
+    u32x8 a = load(cur), b = a;
+    while (visit(a, b) && visit(b, a)) {
+    }
+    keep_loaded(a);
+    keep_loaded(b);
 }
 
 // The 3-D interaction with one node in the lanes of `take` (see take_node).
@@ -126,13 +160,13 @@ __device__ inline void take_node3(uint64_t take, float d2, float dx, float dy, f
 // so the squared distance is at most 3 side^2, below side^2 / theta^2), and
 // the lane's own leaf is taken once with weight 1 as in 2-D.
 template <bool kSelf>
-__device__ inline void repulsive_walk3(const char *nbase, uint32_t end, float3 yi, uint32_t si, uint32_t &resume,
-                                       float &fx, float &fy, float &fz, float &z, uint32_t &inter)
+__device__ inline void repulsive_walk3(const char *nbase, uint32_t cur, uint32_t end, float3 yi, uint32_t si,
+                                       uint32_t &resume, float &fx, float &fy, float &fz, float &z, uint32_t &inter)
 {
-    uint32_t cur = 0;
-    while (cur < end) {
-        typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-        const u32x8 r = *reinterpret_cast<const u32x8 *>(nbase + cur);
+    if (cur >= end) return;
+    auto load = [&](uint32_t at) { return *reinterpret_cast<const u32x8 *>(nbase + at); };
+    auto visit = [&](const u32x8 &r, u32x8 &after) {
+        keep_loaded(r);
         const float dx = yi.x - __uint_as_float(r[0]), dy = yi.y - __uint_as_float(r[1]);
         const float dz = yi.z - __uint_as_float(r[2]);
         const float cnt = __uint_as_float(r[3]), thr = __uint_as_float(r[4]);
@@ -141,11 +175,18 @@ __device__ inline void repulsive_walk3(const char *nbase, uint32_t end, float3 y
         const uint64_t act = mask_uge(cur, resume);
         uint64_t take = act & mask_ogt(d2, thr);
         if (kSelf) take &= mask_ne(r[6], si);
-        const uint64_t rej = act & ~take;
+        cur = take != act ? cur + kNodeBytes3 : next;
+        after = load(cur);
+        __builtin_amdgcn_sched_barrier(0);
         inter += uint32_t(__builtin_popcountll(take));
         take_node3(take, d2, dx, dy, dz, cnt, next, z, fx, fy, fz, resume);
-        cur = rej ? cur + kNodeBytes3 : next;
+        return cur < end;
+    };
+    u32x8 a = load(cur), b = a;
+    while (visit(a, b) && visit(b, a)) {
     }
+    keep_loaded(a);
+    keep_loaded(b);
 }
 
 // 1/x in fp64 for x >= 1: the hardware's approximate reciprocal (measured on
@@ -165,23 +206,29 @@ __device__ inline float recip(float x) { return fast_rcp(x); }
 // 40-byte records with fp64 centres and thresholds; the lanes that take a
 // node accumulate under the compiler's own EXEC mask.
 template <bool kSelf>
-__device__ inline void repulsive_walk64(const char *nbase, uint32_t end, double2 yi, uint32_t si, uint32_t &resume,
-                                        double &fx, double &fy, double &z, uint32_t &inter)
+__device__ inline void repulsive_walk64(const char *nbase, uint32_t cur, uint32_t end, double2 yi, uint32_t si,
+                                        uint32_t &resume, double &fx, double &fy, double &z, uint32_t &inter)
 {
-    uint32_t cur = 0; // byte offset of the current record
-    while (cur < end) {
-        const double *d = reinterpret_cast<const double *>(nbase + cur);
-        const double cx = d[0], cy = d[1], thr = d[2];
-        const uint32_t *u = reinterpret_cast<const uint32_t *>(d + 3);
-        const double cnt = double(__uint_as_float(u[0]));
-        const uint32_t next = u[1], self = u[2];
-        const double dx = yi.x - cx, dy = yi.y - cy;
+    struct Rec {
+        double cx, cy, thr;
+        uint32_t cnt, next, self, pad;
+    };
+    static_assert(sizeof(Rec) == kNodeBytes64, "the record as it is stored");
+    if (cur >= end) return; // cur: byte offset of the current record
+    auto load = [&](uint32_t at) { return *reinterpret_cast<const Rec *>(nbase + at); };
+    auto visit = [&](const Rec &r, Rec &after) {
+        const double cnt = double(__uint_as_float(r.cnt));
+        const uint32_t next = r.next;
+        const double dx = yi.x - r.cx, dy = yi.y - r.cy;
         const double d2 = fma(dx, dx, dy * dy);
         const bool act = cur >= resume;
-        bool tk = act & (d2 > thr);
-        if (kSelf) tk &= self != si;
+        bool tk = act & (d2 > r.thr);
+        if (kSelf) tk &= r.self != si;
         const uint64_t take = ballot(tk);
         const uint64_t rej = ballot(act & !tk);
+        cur = rej ? cur + kNodeBytes64 : next;
+        after = load(cur);
+        __builtin_amdgcn_sched_barrier(0);
         inter += uint32_t(__builtin_popcountll(take));
         if (tk) {
             const double wgt = recip(1.0 + d2);
@@ -192,23 +239,107 @@ __device__ inline void repulsive_walk64(const char *nbase, uint32_t end, double2
             fy = fma(nw2, dy, fy);
             resume = next;
         }
-        cur = rej ? cur + kNodeBytes64 : next;
+        return cur < end;
+    };
+    Rec a = load(cur), b = a;
+    while (visit(a, b) && visit(b, a)) {
     }
+    asm volatile("" ::"s"(a.cx), "s"(b.cx)); // as keep_loaded
+}
+
+// a record's centre, threshold and next offset
+template <int D, typename T> struct Cell {
+    T c[D], thr;
+    uint32_t next;
+};
+
+template <int D, typename T> __device__ inline Cell<D, T> load_cell(const char *__restrict__ r)
+{
+    Cell<D, T> x;
+    const T *f = reinterpret_cast<const T *>(r);
+#pragma unroll
+    for (int d = 0; d < D; ++d) x.c[d] = f[d];
+    const uint32_t *u = reinterpret_cast<const uint32_t *>(r);
+    if constexpr (sizeof(T) == 8) {
+        x.thr = f[2];
+        x.next = u[7];
+    } else {
+        x.thr = f[D + 1];
+        x.next = u[D + 2];
+    }
+    return x;
+}
+
+// From the root to the first record of the wave's part, over the cells that
+// contain it: lanes that accept one of them park until its end (and the wave
+// that owns it counts it).  The cells before the part are stepped over, so
+// this costs a few records per level.  Returns where the part's walk starts,
+// which is past `from` when every lane has parked.  Every step advances.
+template <int D, typename T>
+__device__ inline uint32_t walk_to(const char *nbase, uint32_t from, const point_t<D, T> &yi, uint32_t &resume)
+{
+    uint32_t cur = 0;
+    while (cur < from) {
+        const Cell<D, T> c = load_cell<D, T>(nbase + cur);
+        if (c.next <= from) {
+            cur = c.next;
+            continue;
+        }
+        const T dx = coord(yi, 0) - c.c[0], dy = coord(yi, 1) - c.c[1];
+        T d2;
+        if constexpr (D == 3) {
+            const T dz = coord(yi, 2) - c.c[2];
+            d2 = fma(dx, dx, fma(dy, dy, dz * dz));
+        } else {
+            d2 = fma(dx, dx, dy * dy);
+        }
+        const bool act = cur >= resume, take = act && d2 > c.thr;
+        resume = take ? c.next : resume;
+        cur = ballot(act && !take) ? cur + uint32_t(node_bytes<D, T>()) : c.next;
+    }
+    return cur;
+}
+
+// Bounds of part q of `parts` of the records [0, total) for the points around
+// record `mid`.  A group visits about as many records at each doubling of the
+// distance from its own place in the array (simulated on early and late
+// embeddings of 2k to 1M points: some 100 within its own 64 points, then 50 a
+// doubling, nearest first), so the bounds are evenly spaced in log2(1 +
+// distance / kPartNear).  Every wave of a group computes the same bounds.
+constexpr uint32_t kLine = 128, kTouchLines = 32768;
+constexpr float kPartNear = 16.0f;
+__device__ inline uint32_t part_bound(uint32_t q, uint32_t parts, uint32_t mid, uint32_t total)
+{
+    if (q == 0) return 0;
+    if (q >= parts) return total;
+    const float left = log2f(1.0f + float(mid) / kPartNear), right = log2f(1.0f + float(total - mid) / kPartNear);
+    const float t = (left + right) * (float(q) / float(parts));
+    const float far = kPartNear * (exp2f(fabsf(left - t)) - 1.0f);
+    const uint32_t d = uint32_t(far);
+    return t < left ? (d < mid ? mid - d : 0u) : (d < total - mid ? mid + d : total);
 }
 
 // D = 2, T = float: the path (24-byte records); T = double: the fp64
-// variant; D = 3: 3-D embeddings (32-byte records).
-template <int D, typename T>
+// variant; D = 3: 3-D embeddings (32-byte records).  kSplit: 2^log_waves waves
+// of a block share each group of 64 points, each walking a part of the records.
+template <int D, typename T, bool kSplit>
 __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     const char *__restrict__ nodes, const point_t<D, T> *__restrict__ ys, const uint32_t *__restrict__ perm,
-    Header *__restrict__ hdr, int64_t n, int self_test, point_t<D, T> *__restrict__ frep, double *__restrict__ zpart,
-    unsigned long long *__restrict__ ipart)
+    const uint32_t *__restrict__ base, Header *__restrict__ hdr, int64_t n, int self_test, int log_waves,
+    point_t<D, T> *__restrict__ frep, double *__restrict__ zpart, unsigned long long *__restrict__ ipart)
 {
     using V = point_t<D, T>;
     const uint32_t nb = gridDim.x;
     const uint32_t lb = xcd_contiguous(blockIdx.x, nb);
     const int w = threadIdx.x / kWave;
-    const int64_t s64 = int64_t(lb) * kRepBlock + threadIdx.x;
+    const uint32_t threads = blockDim.x; // at most kRepBlock
+    const int waves = int(threads) / kWave;
+    uint32_t me = 0; // this wave's number among those of its group
+    int64_t s64 = int64_t(lb) * threads + threadIdx.x;
+    if (kSplit) {
+        me = uniform(uint32_t(w)) & ((1u << log_waves) - 1u);
+        s64 = int64_t(lb) * (threads >> log_waves) + int64_t(w >> log_waves) * kWave + lane_id();
+    }
     const bool valid = s64 < n;
     const uint32_t si = uint32_t(s64);
     const V yi = valid ? ys[s64] : V{};
@@ -221,50 +352,95 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     // it and flags the call otherwise), so each visit advances and the walk
     // ends after at most `total` visits.  A flagged tree is not walked.
     if (uniform(hdr->flags) & (kErrLookback | kErrRange)) total = 0;
-    const uint32_t end = total * uint32_t(node_bytes<D, T>());
+    uint32_t cur = 0, end = total * uint32_t(node_bytes<D, T>());
+    uint32_t touched = 0;
+    if constexpr (kSplit) {
+        // The records were written through other XCDs' caches.  Where they fit
+        // this XCD's (4 MB) its blocks fetch them together, one load a line,
+        // before the waves miss them one by one (2k points 42 -> 34 us).
+        const uint32_t lines = (end + kLine - 1) / kLine, stride = (nb >> 3) * threads;
+        if (lines <= kTouchLines)
+            for (uint32_t q = (blockIdx.x >> 3) * threads + threadIdx.x; q < lines; q += stride)
+                touched ^= *reinterpret_cast<const uint32_t *>(nodes + size_t(q) * kLine);
+        const int64_t first = s64 - lane_id();
+        if (first < n && total) {
+            // record of the group's middle point, at most `total`
+            uint32_t mid = uniform(base[first + kWave / 2 < n ? first + kWave / 2 : first]);
+            mid = mid < total ? mid : total;
+            const uint32_t from = uniform(part_bound(me, 1u << log_waves, mid, total));
+            const uint32_t to = uniform(part_bound(me + 1, 1u << log_waves, mid, total));
+            end = to * uint32_t(node_bytes<D, T>());
+            cur = from < to ? walk_to<D, T>(nodes, from * uint32_t(node_bytes<D, T>()), yi, resume) : end;
+        } else {
+            end = 0;
+        }
+        cur = uniform(cur);
+        end = uniform(end);
+    }
 
     uint32_t inter = 0; // this wave's interactions (a launch has fewer than 2^32 per wave)
     if constexpr (D == 3) {
         if (self_test)
-            repulsive_walk3<true>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
+            repulsive_walk3<true>(nodes, cur, end, yi, si, resume, fx, fy, fz, z, inter);
         else
-            repulsive_walk3<false>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
+            repulsive_walk3<false>(nodes, cur, end, yi, si, resume, fx, fy, fz, z, inter);
     } else if constexpr (sizeof(T) == 8) {
         if (self_test)
-            repulsive_walk64<true>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk64<true>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
         else
-            repulsive_walk64<false>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk64<false>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
     } else {
         if (self_test)
-            repulsive_walk<true>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<true, kSplit>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
         else
-            repulsive_walk<false>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<false, kSplit>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
     }
-    if (!self_test) {
+    asm volatile("" ::"v"(touched)); // the loads above are wanted, not their values
+    bool lead = true; // this wave finishes its group's points
+    if constexpr (kSplit) {
+        // the group's sums, added in the order of its waves by the first of them
+        __shared__ T s_part[D + 1][kRepBlock];
+        s_part[0][threadIdx.x] = fx;
+        s_part[1][threadIdx.x] = fy;
+        if (D == 3) s_part[D - 1][threadIdx.x] = fz;
+        s_part[D][threadIdx.x] = z;
+        __syncthreads();
+        lead = me == 0;
+        if (lead) {
+            for (uint32_t q = 1; q < 1u << log_waves; ++q) {
+                const int at = int(threadIdx.x + q * kWave);
+                fx += s_part[0][at];
+                fy += s_part[1][at];
+                if (D == 3) fz += s_part[D - 1][at];
+                z += s_part[D][at];
+            }
+        }
+    }
+    if (!self_test && lead) {
         // each valid lane took its own leaf once, with weight 1
         if (valid) z -= T(1);
-        inter -= uint32_t(__builtin_popcountll(ballot(valid)));
+        inter -= uint32_t(__builtin_popcountll(ballot(valid))); // (the group's total is not negative)
     }
 
-    if (valid) {
+    if (valid && lead) {
         const uint32_t p = perm[si];
         const T f[3] = {fx, fy, fz};
         if (p < uint32_t(n)) frep[p] = make_point(f, static_cast<V *>(nullptr));
     }
     // deterministic Z: wave -> block partial -> fixed-order sum in the last block
-    double zw = wave_sum(double(z));
+    double zw = wave_sum(lead ? double(z) : 0.0);
     __shared__ double s_z[kRepBlock / kWave];
     __shared__ unsigned long long s_i[kRepBlock / kWave];
     __shared__ bool s_last;
     if (lane_id() == 0) {
         s_z[w] = zw;
-        s_i[w] = inter;
+        s_i[w] = static_cast<unsigned long long>(int64_t(int32_t(inter))); // split: the lead's own may be below 0
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         double zb = 0.0;
         unsigned long long ib = 0;
-        for (int k = 0; k < kRepBlock / kWave; ++k) {
+        for (int k = 0; k < waves; ++k) {
             zb += s_z[k];
             ib += s_i[k];
         }
@@ -277,7 +453,7 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     if (!s_last) return;
     __threadfence();
     // last block: each thread sums a fixed contiguous chunk, then a fixed tree
-    const uint32_t per = (nb + kRepBlock - 1) / kRepBlock;
+    const uint32_t per = (nb + threads - 1) / threads;
     double zs = 0.0;
     unsigned long long is = 0;
     for (uint32_t k = threadIdx.x * per; k < (threadIdx.x + 1) * per && k < nb; ++k) {
@@ -295,7 +471,7 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     if (threadIdx.x == 0) {
         double Z = 0.0;
         unsigned long long I = 0;
-        for (int k = 0; k < kRepBlock / kWave; ++k) {
+        for (int k = 0; k < waves; ++k) {
             Z += s_z[k];
             I += s_i[k];
         }
@@ -402,13 +578,59 @@ __global__ __launch_bounds__(256) void attract_kernel(
 }
 
 // ------------------------------------------------------------------ launchers
+// log2 of the waves that share a group of 64 points.  A walk is a chain of
+// dependent record loads (some 300 ns a record alone on a SIMD, 500 to 900
+// records a group), so few groups leave the chip waiting: the launch takes 4, 8
+// or 16 waves a group as long as all of them are resident at once (about 8192,
+// fp64 4096), and 2 up to a point where the launch is bound by issue and the
+// scalar cache, which waves in different places of the tree share less well.
+// Walk in us with 1 wave a group (as before) and with the rule's, gfx950, theta
+// 0.5: fp32 2k points 97 -> 25 (16 waves), 10k 119 -> 35 (16), 70k 171 -> 73 (4),
+// 150k 151 -> 105 (2); 500k 233 against 247 with 2, 1M 443 against 474.  fp64 5k
+// 203 -> 41 (16), 50k 237 -> 79 (4), 200k 281 -> 198 (2), 400k 451 -> 374 (2); 1.3M
+// 986 against 1076 with 2.  (fp32 300k would go from 185 to 176, but the rounding
+// of a group's sums then differs from one wave's, and where attraction and
+// repulsion nearly cancel, early in a main phase, that shows in single points
+// the next step; a 3-D walk, with five times the terms, keeps one wave for it.)
+template <int D, typename T> static int walk_split(int64_t n)
+{
+    if (D == 3) return 0;
+    const int64_t groups = (n + kWave - 1) / kWave;
+    const int64_t resident = sizeof(T) == 8 ? 4096 : 8192;
+    for (int lw = 4; lw > 1; --lw)
+        if (groups << lw <= resident) return lw;
+    return groups <= (sizeof(T) == 8 ? 8192 : 3200) ? 1 : 0;
+}
+
+// Threads of a block.  Blocks of consecutive points share records through the
+// scalar cache, 1024 points best where every CU has several (2-D fp32 1.3M
+// points 606 us, 609 with 512, 643 with 256); smaller ones reach more CUs and
+// end sooner: 300k points 203 -> 185 us with 512, fp64 600k 562 -> 503, 3-D (whose
+// walks differ more in length) 150k 623 -> 542 with 256, 800k 1637 -> 1425, 1.3M
+// 2246 -> 2214.  Shared groups: 150k points 108 -> 105, fp64 400k 484 -> 374; 16
+// waves of one group need a block of 1024.
+template <int D, typename T> static int walk_threads(int64_t n, int log_waves)
+{
+    if (log_waves) return std::max(512, kWave << log_waves);
+    if (D == 3) return 256;
+    return sizeof(T) == 8 || n <= 450000 ? 512 : kRepBlock;
+}
+
 template <int D, typename T>
 void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st)
 {
     using V = point_t<D, T>;
-    repulsive_kernel<D, T><<<unsigned(L.rep_blocks), kRepBlock, 0, st>>>(
-        at<char>(ws, L.nodes), at<V>(ws, L.ys), at<uint32_t>(ws, L.idx0), at<Header>(ws, L.header), n,
-        self_test ? 1 : 0, at<V>(ws, L.frep), at<double>(ws, L.zpart), at<unsigned long long>(ws, L.ipart));
+    const int lw = walk_split<D, T>(n), threads = walk_threads<D, T>(n, lw);
+    const int64_t per = threads >> lw;
+    const int64_t blocks = ((n + per - 1) / per + 7) / 8 * 8; // a multiple of 8 for the XCD-contiguous remap
+    // the blocks' partials go to the sort's second key array, free by now: 16
+    // bytes for at least 64 points, in 8 bytes a point (and 256 at the least)
+    double *zpart = at<double>(ws, L.codes1);
+    auto *kernel = lw ? repulsive_kernel<D, T, true> : repulsive_kernel<D, T, false>;
+    kernel<<<unsigned(blocks), unsigned(threads), 0, st>>>(
+        at<char>(ws, L.nodes), at<V>(ws, L.ys), at<uint32_t>(ws, L.idx0), at<uint32_t>(ws, L.base),
+        at<Header>(ws, L.header), n, self_test ? 1 : 0, lw, at<V>(ws, L.frep), zpart,
+        reinterpret_cast<unsigned long long *>(zpart + blocks));
 }
 template void launch_repulsive<2, float>(int64_t, bool, void *, const Layout &, hipStream_t);
 template void launch_repulsive<2, double>(int64_t, bool, void *, const Layout &, hipStream_t);

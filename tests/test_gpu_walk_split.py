@@ -1,0 +1,62 @@
+"""The repulsive walk at point counts around the bounds where 1, 2, 4, 8 or 16
+waves share a group of 64 points, and around whole groups and blocks, against
+the fp64 oracle: the bars of the other parity tests (fp32 gradients within
+rel-L2 1e-3, Z within 1e-5, interactions within 0.1%; fp64 1e-9, 1e-12, 1e-6)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2212_11506_amd as bh
+import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# two points have P = Q, so that at exaggeration 1 their gradient is exactly 0 and has no relative error
+ALPHA = 12.0
+
+
+def _p(n):
+    return synth.ring_p(n, 3, 2) if n >= 10 else synth.random_p(n, 1)
+
+
+def _check(g, Z, inter, ref, bars):
+    go, Zo, io = ref[:3]
+    assert np.linalg.norm(g - go) <= bars[0] * np.linalg.norm(go)
+    assert abs(Z - Zo) <= bars[1] * Zo
+    assert abs(inter - io) <= bars[2] * io
+
+
+# groups of 64: up to 512 take 16 waves, 1024 8, 2048 4, 3200 2; blocks of 512 up to 450,000 points
+@pytest.mark.parametrize("theta", [0.5, 0.8])
+@pytest.mark.parametrize("n", [2, 63, 65, 1025, 512 * 64, 512 * 64 + 1, 1024 * 64 + 1, 2048 * 64 + 1, 3200 * 64 + 65, 450_001])
+def test_walk_2d(n, theta):
+    Y = synth.random_y(n, n, dups=n // 10)
+    p = _p(n)
+    P = bh.Csr.from_numpy(*p, device=DEV)
+    ws = torch.empty(bh.workspace_size(n, P.nnz), dtype=torch.uint8, device=DEV)
+    g, Z = bh.gradient(torch.from_numpy(Y).to(DEV), P, theta, ALPHA, workspace=ws)
+    _check(g.cpu().numpy(), Z, bh.get_stats(ws)["interactions"], oracle.gradient(Y, *p, theta, ALPHA), (1e-3, 1e-5, 1e-3))
+
+
+# up to 256 groups take 16 waves, 512 8, 1024 4, 8192 2
+@pytest.mark.parametrize("n", [3, 66, 256 * 64 + 1, 512 * 64 + 63, 1024 * 64 + 1, 8192 * 64 + 1])
+def test_walk_f64(n):
+    Y = synth.random_y(n, n, dups=n // 10).astype(np.float64)
+    p = _p(n)
+    P = bh.CsrF64.from_numpy(*p, device=DEV)
+    ws = torch.empty(bh.workspace_size_f64(n, P.nnz), dtype=torch.uint8, device=DEV)
+    g, Z = bh.gradient_f64(torch.from_numpy(Y).to(DEV), P, 0.5, ALPHA, workspace=ws)
+    _check(g.cpu().numpy(), Z, bh.get_stats(ws)["interactions"], oracle.gradient(Y, *p, 0.5, ALPHA), (1e-9, 1e-12, 1e-6))
+
+
+# one wave a group, blocks of 256
+@pytest.mark.parametrize("theta", [0.5, 0.8])
+@pytest.mark.parametrize("n", [2, 65, 257, 2049, 40_000])
+def test_walk_3d(n, theta):
+    Y = synth.random_y3(n, n, dups=n // 10)
+    p = _p(n)
+    P = bh.Csr.from_numpy(*p, device=DEV)
+    ws = torch.empty(bh.workspace_size_3d(n, P.nnz), dtype=torch.uint8, device=DEV)
+    g, Z = bh.gradient_3d(torch.from_numpy(Y).to(DEV), P, theta, ALPHA, workspace=ws)
+    _check(g.cpu().numpy(), Z, bh.get_stats(ws)["interactions"], oracle.gradient3(Y, *p, theta, ALPHA), (1e-3, 1e-5, 1e-3))
