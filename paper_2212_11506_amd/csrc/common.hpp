@@ -231,6 +231,39 @@ __device__ inline double wave_max(double v)
     return v;
 }
 
+// Bitonic sort of 64 kS distinct keys held by a wave in registers, ascending:
+// slot x = 64 q + lane is v[q] of that lane.  Partners fewer than 64 slots apart
+// are exchanged by lane shuffles, farther ones within the lane.
+template <int kS> __device__ inline void wave_sort(uint32_t (&v)[kS])
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int size = 2; size <= kS * kWave; size <<= 1) {
+#pragma unroll
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            if (stride >= kWave) {
+                const int qs = stride / kWave;
+#pragma unroll
+                for (int q = 0; q < kS; ++q) {
+                    if (q & qs) continue;
+                    const bool up = ((q * kWave + lane) & size) == 0;
+                    const uint32_t a = v[q], b = v[q | qs];
+                    v[q] = up ? min(a, b) : max(a, b);
+                    v[q | qs] = up ? max(a, b) : min(a, b);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < kS; ++q) {
+                    const uint32_t o = uint32_t(__shfl_xor(int(v[q]), stride, kWave));
+                    const bool up = ((q * kWave + lane) & size) == 0;
+                    const bool low = (lane & stride) == 0;
+                    v[q] = (low == up) ? min(v[q], o) : max(v[q], o);
+                }
+            }
+        }
+    }
+}
+
 __device__ inline float vmin(float a, float b) { return fminf(a, b); }
 __device__ inline float vmax(float a, float b) { return fmaxf(a, b); }
 __device__ inline double vmin(double a, double b) { return fmin(a, b); }

@@ -424,9 +424,7 @@ __global__ __launch_bounds__(256) void aff_search_quad_kernel(const float *__res
 // 2. own rows in column order, one wave per row (four rows per block).  The
 // entries, packed as column * 256 + neighbour position (distinct, so the
 // order is strict and ties keep the neighbour order) and padded with all-ones
-// to 64 kS slots, are sorted by a bitonic network held in registers: slot x
-// = 64 q + lane; partners fewer than 64 slots apart are exchanged by lane
-// shuffles, farther ones within the lane.  Writes the row in column order
+// to 64 kS slots, are sorted in registers (wave_sort).  Writes the row in column order
 // (scol) and each entry's neighbour position (sorig), and flags columns
 // outside [0, n), the row itself and repeated neighbours.  kS: 1, 2 or 4 (k
 // <= 64 kS).
@@ -435,7 +433,6 @@ __global__ __launch_bounds__(256) void aff_own_sort_kernel(const int32_t *__rest
                                                            int32_t *__restrict__ scol, uint8_t *__restrict__ sorig,
                                                            Header *__restrict__ hdr)
 {
-    constexpr int kN = kS * kWave;
     const int w = threadIdx.x / kWave, lane = lane_id();
     const int64_t i = int64_t(blockIdx.x) * (256 / kWave) + w;
     if (i >= n) return; // whole waves
@@ -451,31 +448,7 @@ __global__ __launch_bounds__(256) void aff_own_sort_kernel(const int32_t *__rest
             v[q] = ((c < 0xffffffu ? c : 0xffffffu) << 8) | uint32_t(e);
         }
     }
-#pragma unroll
-    for (int size = 2; size <= kN; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride >= kWave) {
-                const int qs = stride / kWave;
-#pragma unroll
-                for (int q = 0; q < kS; ++q) {
-                    if (q & qs) continue;
-                    const bool up = ((q * kWave + lane) & size) == 0;
-                    const uint32_t a = v[q], b = v[q | qs];
-                    v[q] = up ? min(a, b) : max(a, b);
-                    v[q | qs] = up ? max(a, b) : min(a, b);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < kS; ++q) {
-                    const uint32_t o = uint32_t(__shfl_xor(int(v[q]), stride, kWave));
-                    const bool up = ((q * kWave + lane) & size) == 0;
-                    const bool low = (lane & stride) == 0;
-                    v[q] = (low == up) ? min(v[q], o) : max(v[q], o);
-                }
-            }
-        }
-    }
+    wave_sort(v);
 #pragma unroll
     for (int q = 0; q < kS; ++q) {
         const int x = q * kWave + lane;
