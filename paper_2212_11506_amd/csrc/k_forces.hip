@@ -58,6 +58,20 @@ __device__ inline void take_node(uint64_t take, float d2, float dx, float dy, fl
                  : "scc");
 }
 
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+
+// 32 bytes at a record: one scalar load
+__device__ inline u32x8 load_record(const char *nbase, uint32_t at)
+{
+    return *reinterpret_cast<const u32x8 *>(nbase + at);
+}
+
+// The words of a record that a visit does not read count as read when it
+// starts: their registers would be given to other values while the load that
+// fills them is in flight, and the wave would wait for it there.  After a loop
+// they keep its last load from being moved behind the exit test.
+__device__ inline void keep_loaded(const u32x8 &r) { asm volatile("" ::"s"(r[5]), "s"(r[6]), "s"(r[7])); }
+
 // One lane per point.  Every visit runs the same code on a 24-byte record read
 // with one scalar load: a single point is a node whose threshold (-1) every
 // lane passes, and a bucket of identical points is a cell whose children are
@@ -74,28 +88,19 @@ __device__ inline void take_node(uint64_t take, float d2, float dx, float dy, fl
 // leaf's position with the lane's.
 //
 // A visit is a chain: the record's scalar load, the compares, the choice of the
-// next record.  The next record is loaded as soon as it is chosen, before the
-// accumulation of the one in hand, which takes as long as the compares; two
-// visits a round alternate between two sets of registers, so nothing is moved.
-// The load past the last record stays inside the array's padding.  (Walks that
-// several waves share, fp64 and 3-D: fp64 400k points 451 -> 424 us, 3-D 150k 718
-// -> 622.  With 8 waves a SIMD the 2-D fp32 walk is bound by issue and its
-// simpler loop is as fast: 1M points 447 us against 455.)
-typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-
-// The words of a record that a visit does not read count as read when it
-// starts: their registers would be given to other values while the load that
-// fills them is in flight, and the wave would wait for it there.  After the
-// loop they keep its last load from being moved behind the exit test.
-__device__ inline void keep_loaded(const u32x8 &r) { asm volatile("" ::"s"(r[5]), "s"(r[6]), "s"(r[7])); }
-
+// next record.  With kAhead the next record is loaded as soon as it is chosen,
+// before the accumulation of the one in hand, which takes as long as the
+// compares; two visits a round alternate between two sets of registers, so
+// nothing is moved.  The load past the last record stays inside the array's
+// padding.  (3-D 150k points 718 -> 622 us, fp64 400k 451 -> 424, 2-D fp32 150k 151 ->
+// 139.  With 8 waves a SIMD the 2-D fp32 walk is bound by issue and the simple loop
+// as fast: 1M points 447 us against 455.)
 template <bool kSelf, bool kAhead>
-__device__ inline void repulsive_walk(const char *nbase, uint32_t cur, uint32_t end, float2 yi, uint32_t si,
-                                      uint32_t &resume, float &fx, float &fy, float &z, uint32_t &inter)
+__device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi, uint32_t si, uint32_t &resume,
+                                      float &fx, float &fy, float &z, uint32_t &inter)
 {
-    if (cur >= end) return; // cur: byte offset of the current record
-    // the record and 8 bytes beyond it: one 32-byte scalar load
-    auto load = [&](uint32_t at) { return *reinterpret_cast<const u32x8 *>(nbase + at); };
+    uint32_t cur = 0; // byte offset of the current record
+    if (cur >= end) return;
     auto visit = [&](const u32x8 &r, u32x8 &after) {
         if (kAhead) keep_loaded(r);
         const float cx = __uint_as_float(r[0]), cy = __uint_as_float(r[1]);
@@ -109,7 +114,7 @@ __device__ inline void repulsive_walk(const char *nbase, uint32_t cur, uint32_t 
         // the first child follows its cell; no lane descends: jump past the subtree
         cur = take != act ? cur + kNodeBytes : next;
         if (kAhead) {
-            after = load(cur);
+            after = load_record(nbase, cur);
             __builtin_amdgcn_sched_barrier(0);
         }
         inter += uint32_t(__builtin_popcountll(take));
@@ -118,11 +123,11 @@ __device__ inline void repulsive_walk(const char *nbase, uint32_t cur, uint32_t 
     };
     if (!kAhead) {
         u32x8 none;
-        while (visit(load(cur), none)) {
+        while (visit(load_record(nbase, cur), none)) {
         }
         return;
     }
-    u32x8 a = load(cur), b = a;
+    u32x8 a = load_record(nbase, cur), b = a;
     while (visit(a, b) && visit(b, a)) {
     }
     keep_loaded(a);
@@ -160,11 +165,11 @@ __device__ inline void take_node3(uint64_t take, float d2, float dx, float dy, f
 // so the squared distance is at most 3 side^2, below side^2 / theta^2), and
 // the lane's own leaf is taken once with weight 1 as in 2-D.
 template <bool kSelf>
-__device__ inline void repulsive_walk3(const char *nbase, uint32_t cur, uint32_t end, float3 yi, uint32_t si,
-                                       uint32_t &resume, float &fx, float &fy, float &fz, float &z, uint32_t &inter)
+__device__ inline void repulsive_walk3(const char *nbase, uint32_t end, float3 yi, uint32_t si, uint32_t &resume,
+                                       float &fx, float &fy, float &fz, float &z, uint32_t &inter)
 {
+    uint32_t cur = 0;
     if (cur >= end) return;
-    auto load = [&](uint32_t at) { return *reinterpret_cast<const u32x8 *>(nbase + at); };
     auto visit = [&](const u32x8 &r, u32x8 &after) {
         keep_loaded(r);
         const float dx = yi.x - __uint_as_float(r[0]), dy = yi.y - __uint_as_float(r[1]);
@@ -176,13 +181,13 @@ __device__ inline void repulsive_walk3(const char *nbase, uint32_t cur, uint32_t
         uint64_t take = act & mask_ogt(d2, thr);
         if (kSelf) take &= mask_ne(r[6], si);
         cur = take != act ? cur + kNodeBytes3 : next;
-        after = load(cur);
+        after = load_record(nbase, cur);
         __builtin_amdgcn_sched_barrier(0);
         inter += uint32_t(__builtin_popcountll(take));
         take_node3(take, d2, dx, dy, dz, cnt, next, z, fx, fy, fz, resume);
         return cur < end;
     };
-    u32x8 a = load(cur), b = a;
+    u32x8 a = load_record(nbase, cur), b = a;
     while (visit(a, b) && visit(b, a)) {
     }
     keep_loaded(a);
@@ -319,6 +324,175 @@ __device__ inline uint32_t part_bound(uint32_t q, uint32_t parts, uint32_t mid, 
     return t < left ? (d < mid ? mid - d : 0u) : (d < total - mid ? mid + d : total);
 }
 
+// ---- fp32 groups shared by several waves
+// The waves of a group list what their parts of the records contribute, an entry
+// {centre, count; mask of the lanes that take it}, and the group's first wave then
+// adds the entries up in the order of the records: the same sums, bit for bit, as
+// one wave's walk.  (Partial sums of the parts would round differently, which
+// where attraction and repulsion nearly cancel shows in single points a step
+// later.)  Listing leaves out the reciprocal and the sums, 10 vector instructions
+// a visit instead of 14, and adding up has no chain but the sums.
+constexpr int kListRoom = 256; // entries of a wave's list
+
+struct Lists { // in LDS, `waves` lists of kListRoom entries
+    float4 *c;
+    uint32_t *lo, *hi;
+    int *len, *done, *part;
+    static size_t bytes(int waves) { return size_t(waves) * (kListRoom * 24 + 12); }
+    __device__ Lists(char *m, int waves)
+    {
+        c = reinterpret_cast<float4 *>(m);
+        lo = reinterpret_cast<uint32_t *>(c + waves * kListRoom);
+        hi = lo + waves * kListRoom;
+        len = reinterpret_cast<int *>(hi + waves * kListRoom);
+        done = len + waves;
+        part = done + waves;
+    }
+};
+
+// Walks on from `cur` until the part ends or the list is full; returns the list's length.
+template <int D, bool kSelf>
+__device__ inline int walk_list(const char *nbase, uint32_t &cur, uint32_t end, const point_t<D, float> &yi, uint32_t si,
+                                uint32_t &resume, uint32_t &inter, const Lists &l, int first, int len)
+{
+    constexpr uint32_t kBytes = uint32_t(node_bytes<D, float>());
+    uint32_t rec = 0, lo = 0, hi = 0; // the last up to 64 entries, one a lane
+    int fill = 0;
+    auto visit = [&](const u32x8 &r, u32x8 &after) {
+        keep_loaded(r);
+        asm volatile("" ::"s"(r[D])); // (the count)
+        const float dx = coord(yi, 0) - __uint_as_float(r[0]), dy = coord(yi, 1) - __uint_as_float(r[1]);
+        float d2;
+        if constexpr (D == 3) {
+            const float dz = coord(yi, 2) - __uint_as_float(r[2]);
+            d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        } else {
+            d2 = fmaf(dx, dx, dy * dy);
+        }
+        const float thr = __uint_as_float(r[D + 1]);
+        const uint32_t next = r[D + 2], at = cur;
+        const uint64_t act = mask_uge(cur, resume);
+        uint64_t take = act & mask_ogt(d2, thr);
+        if (kSelf) take &= mask_ne(r[D + 3], si);
+        cur = take != act ? cur + kBytes : next;
+        after = load_record(nbase, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        inter += uint32_t(__builtin_popcountll(take));
+        // the lanes that take it park, and lane `fill` keeps the entry (a record that no
+        // lane takes is overwritten by the next)
+        uint64_t saved;
+        asm volatile("s_mov_b32 m0, %[fill]\n\t"
+                     "s_and_saveexec_b64 %[sv], %[take]\n\t"
+                     "v_mov_b32 %[res], %[next]\n\t"
+                     "s_mov_b64 exec, %[sv]\n\t"
+                     "v_writelane_b32 %[rec], %[at], m0\n\t"
+                     "v_writelane_b32 %[lo], %[tlo], m0\n\t"
+                     "v_writelane_b32 %[hi], %[thi], m0"
+                     : [res] "+v"(resume), [sv] "=&s"(saved), [rec] "+v"(rec), [lo] "+v"(lo), [hi] "+v"(hi)
+                     : [take] "s"(take), [next] "s"(next), [fill] "s"(fill), [at] "s"(at), [tlo] "s"(uint32_t(take)),
+                       [thi] "s"(uint32_t(take >> 32))
+                     : "scc", "m0");
+        fill += take != 0 ? 1 : 0;
+        return cur < end && fill < kWave;
+    };
+    while (cur < end && len + kWave <= kListRoom) {
+        u32x8 a = load_record(nbase, cur), b = a;
+        while (visit(a, b) && visit(b, a)) {
+        }
+        keep_loaded(a);
+        keep_loaded(b);
+        asm volatile("" ::"s"(a[D]), "s"(b[D]));
+        if (lane_id() < fill) {
+            const int to = first + len + lane_id();
+            const float *r = reinterpret_cast<const float *>(nbase + rec);
+            l.c[to] = make_float4(r[0], r[1], r[2], D == 3 ? r[3] : 0.0f);
+            l.lo[to] = lo;
+            l.hi[to] = hi;
+        }
+        len += fill;
+        fill = 0;
+    }
+    return len;
+}
+
+// Adds up `len` listed entries in their order.  An entry is read by all lanes at
+// once; a lane outside its mask counts it 0 times, which leaves its sums as they
+// are.
+template <int D>
+__device__ inline void add_list(const Lists &l, int first, int len, const point_t<D, float> &yi, float &fx, float &fy,
+                                float &fz, float &z)
+{
+    const float4 *c = l.c + first;
+    const uint32_t *mask = (lane_id() < 32 ? l.lo : l.hi) + first;
+    const uint32_t bit = lane_id() & 31;
+    auto add = [&](const float4 &e, uint32_t m) {
+        const float cnt = (m >> bit) & 1u ? (D == 3 ? e.w : e.z) : 0.0f;
+        const float dx = coord(yi, 0) - e.x, dy = coord(yi, 1) - e.y;
+        float dz = 0.0f, d2;
+        if constexpr (D == 3) {
+            dz = coord(yi, 2) - e.z;
+            d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        } else {
+            d2 = fmaf(dx, dx, dy * dy);
+        }
+        const float w = fast_rcp(1.0f + d2);
+        float t = cnt * w;
+        z = fmaf(cnt, w, z);
+        t = t * w;
+        fx = fmaf(t, dx, fx);
+        fy = fmaf(t, dy, fy);
+        if constexpr (D == 3) fz = fmaf(t, dz, fz);
+    };
+    constexpr int kAtOnce = 8;
+    int k = 0;
+    for (; k + kAtOnce <= len; k += kAtOnce) {
+        float4 e[kAtOnce];
+        uint32_t m[kAtOnce];
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q) {
+            e[q] = c[k + q];
+            m[q] = mask[k + q];
+        }
+#pragma unroll
+        for (int q = 0; q < kAtOnce; ++q) add(e[q], m[q]);
+    }
+    for (; k < len; ++k) add(c[k], mask[k]);
+}
+
+// The walk of a group's waves.  Where a list fills up before its part ends, the
+// waves meet, the first adds up what comes next in order, and the part whose
+// list that emptied walks on: at least one part ends or empties its list each
+// round, so the rounds end.
+template <int D, bool kSelf>
+__device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end, const point_t<D, float> &yi,
+                                   uint32_t si, uint32_t me, int log_waves, uint32_t &resume, float &fx, float &fy,
+                                   float &fz, float &z, uint32_t &inter, const Lists &l)
+{
+    const int w = int(uniform(threadIdx.x / kWave)), lead = w - int(me), parts = 1 << log_waves;
+    int len = 0, part = 0; // part: the first one that is not added up yet
+    for (;;) {
+        if (int(me) >= part)
+            len = walk_list<D, kSelf>(nbase, cur, end, yi, si, resume, inter, l, w * kListRoom, len);
+        if (lane_id() == 0) {
+            l.len[w] = len;
+            l.done[w] = cur >= end;
+        }
+        __syncthreads();
+        if (me == 0) {
+            while (part < parts) {
+                add_list<D>(l, (lead + part) * kListRoom, int(uniform(uint32_t(l.len[lead + part]))), yi, fx, fy, fz, z);
+                if (!uniform(uint32_t(l.done[lead + part]))) break; // its list is empty now
+                ++part;
+            }
+            if (lane_id() == 0) l.part[w] = part;
+        }
+        __syncthreads();
+        part = int(uniform(uint32_t(l.part[lead])));
+        if (int(me) == part) len = 0;
+        if (__syncthreads_and(part == parts)) return;
+    }
+}
+
 // D = 2, T = float: the path (24-byte records); T = double: the fp64
 // variant; D = 3: 3-D embeddings (32-byte records).  kSplit: 2^log_waves waves
 // of a block share each group of 64 points, each walking a part of the records.
@@ -326,7 +500,7 @@ template <int D, typename T, bool kSplit>
 __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     const char *__restrict__ nodes, const point_t<D, T> *__restrict__ ys, const uint32_t *__restrict__ perm,
     const uint32_t *__restrict__ base, Header *__restrict__ hdr, int64_t n, int self_test, int log_waves,
-    point_t<D, T> *__restrict__ frep, double *__restrict__ zpart, unsigned long long *__restrict__ ipart)
+    int ahead, point_t<D, T> *__restrict__ frep, double *__restrict__ zpart, unsigned long long *__restrict__ ipart)
 {
     using V = point_t<D, T>;
     const uint32_t nb = gridDim.x;
@@ -379,40 +553,53 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     }
 
     uint32_t inter = 0; // this wave's interactions (a launch has fewer than 2^32 per wave)
-    if constexpr (D == 3) {
+    if constexpr (kSplit && sizeof(T) == 4) {
+        extern __shared__ float4 s_lists[];
+        const Lists lists(reinterpret_cast<char *>(s_lists), waves);
         if (self_test)
-            repulsive_walk3<true>(nodes, cur, end, yi, si, resume, fx, fy, fz, z, inter);
+            walk_shared<D, true>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
         else
-            repulsive_walk3<false>(nodes, cur, end, yi, si, resume, fx, fy, fz, z, inter);
+            walk_shared<D, false>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+    } else if constexpr (D == 3) {
+        if (self_test)
+            repulsive_walk3<true>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
+        else
+            repulsive_walk3<false>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
     } else if constexpr (sizeof(T) == 8) {
         if (self_test)
             repulsive_walk64<true>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
         else
             repulsive_walk64<false>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
+    } else if (ahead) {
+        if (self_test)
+            repulsive_walk<true, true>(nodes, end, yi, si, resume, fx, fy, z, inter);
+        else
+            repulsive_walk<false, true>(nodes, end, yi, si, resume, fx, fy, z, inter);
     } else {
         if (self_test)
-            repulsive_walk<true, kSplit>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<true, false>(nodes, end, yi, si, resume, fx, fy, z, inter);
         else
-            repulsive_walk<false, kSplit>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<false, false>(nodes, end, yi, si, resume, fx, fy, z, inter);
     }
     asm volatile("" ::"v"(touched)); // the loads above are wanted, not their values
     bool lead = true; // this wave finishes its group's points
     if constexpr (kSplit) {
-        // the group's sums, added in the order of its waves by the first of them
-        __shared__ T s_part[D + 1][kRepBlock];
-        s_part[0][threadIdx.x] = fx;
-        s_part[1][threadIdx.x] = fy;
-        if (D == 3) s_part[D - 1][threadIdx.x] = fz;
-        s_part[D][threadIdx.x] = z;
-        __syncthreads();
         lead = me == 0;
-        if (lead) {
-            for (uint32_t q = 1; q < 1u << log_waves; ++q) {
-                const int at = int(threadIdx.x + q * kWave);
-                fx += s_part[0][at];
-                fy += s_part[1][at];
-                if (D == 3) fz += s_part[D - 1][at];
-                z += s_part[D][at];
+        if constexpr (sizeof(T) == 8) {
+            // the group's sums, added in the order of its waves by the first of them
+            // (in fp64 another rounding of the sums shows nowhere)
+            __shared__ T s_part[3][kRepBlock];
+            s_part[0][threadIdx.x] = fx;
+            s_part[1][threadIdx.x] = fy;
+            s_part[2][threadIdx.x] = z;
+            __syncthreads();
+            if (lead) {
+                for (uint32_t q = 1; q < 1u << log_waves; ++q) {
+                    const int at = int(threadIdx.x + q * kWave);
+                    fx += s_part[0][at];
+                    fy += s_part[1][at];
+                    z += s_part[2][at];
+                }
             }
         }
     }
@@ -578,58 +765,60 @@ __global__ __launch_bounds__(256) void attract_kernel(
 }
 
 // ------------------------------------------------------------------ launchers
-// log2 of the waves that share a group of 64 points.  A walk is a chain of
-// dependent record loads (some 300 ns a record alone on a SIMD, 500 to 900
-// records a group), so few groups leave the chip waiting: the launch takes 4, 8
-// or 16 waves a group as long as all of them are resident at once (about 8192,
-// fp64 4096), and 2 up to a point where the launch is bound by issue and the
-// scalar cache, which waves in different places of the tree share less well.
-// Walk in us with 1 wave a group (as before) and with the rule's, gfx950, theta
-// 0.5: fp32 2k points 97 -> 25 (16 waves), 10k 119 -> 35 (16), 70k 171 -> 73 (4),
-// 150k 151 -> 105 (2); 500k 233 against 247 with 2, 1M 443 against 474.  fp64 5k
-// 203 -> 41 (16), 50k 237 -> 79 (4), 200k 281 -> 198 (2), 400k 451 -> 374 (2); 1.3M
-// 986 against 1076 with 2.  (fp32 300k would go from 185 to 176, but the rounding
-// of a group's sums then differs from one wave's, and where attraction and
-// repulsion nearly cancel, early in a main phase, that shows in single points
-// the next step; a 3-D walk, with five times the terms, keeps one wave for it.)
-template <int D, typename T> static int walk_split(int64_t n)
-{
-    if (D == 3) return 0;
-    const int64_t groups = (n + kWave - 1) / kWave;
-    const int64_t resident = sizeof(T) == 8 ? 4096 : 8192;
-    for (int lw = 4; lw > 1; --lw)
-        if (groups << lw <= resident) return lw;
-    return groups <= (sizeof(T) == 8 ? 8192 : 3200) ? 1 : 0;
-}
+// How a walk is launched: log2 of the waves that share a group of 64 points, the
+// threads of a block, and whether one wave's 2-D fp32 walk loads ahead.
+//
+// A walk is a chain of dependent record loads (some 300 ns a record alone on a
+// SIMD, 500 to 900 records a group), so few groups leave the chip waiting, and
+// several waves share one: in fp64 4, 8 or 16 as long as all are resident at
+// once (about 4096), and 2 up to a point where the launch is bound by issue and
+// the scalar cache, which waves in different places of the tree share less
+// well.  In fp32 the listed entries are added up by one wave of a group, so
+// sharing pays only where the walks themselves are many times longer than that.
+// Blocks of consecutive points share records through the scalar cache, 1024
+// points best where every CU has several blocks; smaller ones reach more CUs and
+// end sooner.  Walk in us, gfx950, theta 0.5, the start's in brackets:
+//   fp32  8 waves a group: 2k points (94) 52, 10k (115) 65, 30k (112) 82;
+//         1 wave, ahead, 256 threads: 2k 81, 10k 98, 30k 89, 70k (165) 134, 150k (151)
+//         141, 300k (226) 200, 500k 256; 1024 threads, simple: 500k 235, 1M 447
+//   fp64  5k (203) 41 with 16 waves, 50k (237) 79 with 4, 200k (281) 198 with 2, 400k
+//         (451) 374 with 2; 600k 503 with 1 and 512 threads, 562 with 1024
+//   3-D   5k (328) 181 with 16 waves, 225 with 1; 20k 203 against 208; 1 wave, 256
+//         threads: 50k (397) 299, 150k (718) 539, 800k (1412) 1425 early, 1.3M (2246) 2214
+struct WalkLaunch {
+    int log_waves, threads;
+    bool ahead;
+};
 
-// Threads of a block.  Blocks of consecutive points share records through the
-// scalar cache, 1024 points best where every CU has several (2-D fp32 1.3M
-// points 606 us, 609 with 512, 643 with 256); smaller ones reach more CUs and
-// end sooner: 300k points 203 -> 185 us with 512, fp64 600k 562 -> 503, 3-D (whose
-// walks differ more in length) 150k 623 -> 542 with 256, 800k 1637 -> 1425, 1.3M
-// 2246 -> 2214.  Shared groups: 150k points 108 -> 105, fp64 400k 484 -> 374; 16
-// waves of one group need a block of 1024.
-template <int D, typename T> static int walk_threads(int64_t n, int log_waves)
+template <int D, typename T> static WalkLaunch walk_launch(int64_t n)
 {
-    if (log_waves) return std::max(512, kWave << log_waves);
-    if (D == 3) return 256;
-    return sizeof(T) == 8 || n <= 450000 ? 512 : kRepBlock;
+    const int64_t groups = (n + kWave - 1) / kWave;
+    if (D == 3) return groups <= 128 ? WalkLaunch{4, 1024, true} : WalkLaunch{0, 256, true};
+    if (sizeof(T) == 8) {
+        for (int lw = 4; lw > 1; --lw)
+            if (groups << lw <= 4096) return {lw, std::max(512, kWave << lw), true};
+        return {groups <= 8192 ? 1 : 0, 512, true};
+    }
+    if (groups <= 480) return {3, 512, true};
+    if (groups <= 6400) return {0, 256, true};
+    return {0, kRepBlock, false};
 }
 
 template <int D, typename T>
 void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st)
 {
     using V = point_t<D, T>;
-    const int lw = walk_split<D, T>(n), threads = walk_threads<D, T>(n, lw);
-    const int64_t per = threads >> lw;
+    const WalkLaunch c = walk_launch<D, T>(n);
+    const int64_t per = c.threads >> c.log_waves;
     const int64_t blocks = ((n + per - 1) / per + 7) / 8 * 8; // a multiple of 8 for the XCD-contiguous remap
     // the blocks' partials go to the sort's second key array, free by now: 16
     // bytes for at least 64 points, in 8 bytes a point (and 256 at the least)
     double *zpart = at<double>(ws, L.codes1);
-    auto *kernel = lw ? repulsive_kernel<D, T, true> : repulsive_kernel<D, T, false>;
-    kernel<<<unsigned(blocks), unsigned(threads), 0, st>>>(
+    auto *kernel = c.log_waves ? repulsive_kernel<D, T, true> : repulsive_kernel<D, T, false>;
+    const size_t lds = c.log_waves && sizeof(T) == 4 ? Lists::bytes(c.threads / kWave) : 0;
+    kernel<<<unsigned(blocks), unsigned(c.threads), lds, st>>>(
         at<char>(ws, L.nodes), at<V>(ws, L.ys), at<uint32_t>(ws, L.idx0), at<uint32_t>(ws, L.base),
-        at<Header>(ws, L.header), n, self_test ? 1 : 0, lw, at<V>(ws, L.frep), zpart,
+        at<Header>(ws, L.header), n, self_test ? 1 : 0, c.log_waves, c.ahead ? 1 : 0, at<V>(ws, L.frep), zpart,
         reinterpret_cast<unsigned long long *>(zpart + blocks));
 }
 template void launch_repulsive<2, float>(int64_t, bool, void *, const Layout &, hipStream_t);

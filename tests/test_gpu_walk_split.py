@@ -1,7 +1,8 @@
-"""The repulsive walk at point counts around the bounds where 1, 2, 4, 8 or 16
-waves share a group of 64 points, and around whole groups and blocks, against
-the fp64 oracle: the bars of the other parity tests (fp32 gradients within
-rel-L2 1e-3, Z within 1e-5, interactions within 0.1%; fp64 1e-9, 1e-12, 1e-6)."""
+"""The repulsive walk at point counts around the bounds where several waves share
+a group of 64 points, around whole groups and blocks, and where the waves' lists
+overflow, against the fp64 oracle: the bars of the other parity tests (fp32
+gradients within rel-L2 1e-3, Z within 1e-5, interactions within 0.1%; fp64 1e-9,
+1e-12, 1e-6)."""
 import numpy as np
 import pytest
 import torch
@@ -27,9 +28,10 @@ def _check(g, Z, inter, ref, bars):
     assert abs(inter - io) <= bars[2] * io
 
 
-# groups of 64: up to 512 take 16 waves, 1024 8, 2048 4, 3200 2; blocks of 512 up to 450,000 points
-@pytest.mark.parametrize("theta", [0.5, 0.8])
-@pytest.mark.parametrize("n", [2, 63, 65, 1025, 512 * 64, 512 * 64 + 1, 1024 * 64 + 1, 2048 * 64 + 1, 3200 * 64 + 65, 450_001])
+# groups of 64: up to 480 take 8 waves, up to 6400 blocks of 256 threads; theta 0.05 fills the waves' lists
+@pytest.mark.parametrize("n, theta", [(2, 0.5), (63, 0.8), (65, 0.5), (1025, 0.8), (6000, 0.05), (3001, 0.0), (480 * 64, 0.5),
+                                      (480 * 64, 0.8), (480 * 64 + 1, 0.5), (480 * 64 + 1, 0.8), (6400 * 64, 0.5),
+                                      (6400 * 64 + 1, 0.8)])
 def test_walk_2d(n, theta):
     Y = synth.random_y(n, n, dups=n // 10)
     p = _p(n)
@@ -50,9 +52,9 @@ def test_walk_f64(n):
     _check(g.cpu().numpy(), Z, bh.get_stats(ws)["interactions"], oracle.gradient(Y, *p, 0.5, ALPHA), (1e-9, 1e-12, 1e-6))
 
 
-# one wave a group, blocks of 256
-@pytest.mark.parametrize("theta", [0.5, 0.8])
-@pytest.mark.parametrize("n", [2, 65, 257, 2049, 40_000])
+# up to 128 groups take 16 waves, then blocks of 256 threads
+@pytest.mark.parametrize("n, theta", [(2, 0.5), (65, 0.8), (2049, 0.5), (2000, 0.0), (128 * 64, 0.8), (128 * 64, 0.2),
+                                      (128 * 64 + 1, 0.5), (40_000, 0.8)])
 def test_walk_3d(n, theta):
     Y = synth.random_y3(n, n, dups=n // 10)
     p = _p(n)
