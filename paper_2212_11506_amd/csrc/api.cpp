@@ -773,7 +773,7 @@ int bhtsne_debug_sort_3d(const float *Y, int64_t n, uint64_t *codes, uint64_t *s
     if (rc != BHTSNE_OK) return rc;
     const Layout L = make_layout(n, 0, 4, 3);
     launch_bbox_morton3(Y, n, nullptr, workspace, L, stream);
-    if (codes && hipMemcpyAsync(codes, at<void>(workspace, L.codes0), 8 * size_t(n), hipMemcpyDeviceToDevice,
+    if (codes && hipMemcpyAsync(codes, sort_input(workspace, L), 8 * size_t(n), hipMemcpyDeviceToDevice,
                                 stream) != hipSuccess)
         return BHTSNE_EDEVICE;
     launch_sort_points(n, reinterpret_cast<const float3 *>(Y), workspace, L, stream);
@@ -1170,7 +1170,7 @@ int bhtsne_debug_sort(const float *Y, int64_t n, uint64_t *codes, uint64_t *sort
     const Layout L = make_layout(n, 0);
     launch_bbox(Y, n, workspace, L, stream);
     launch_morton(Y, n, nullptr, workspace, L, stream);
-    if (codes && hipMemcpyAsync(codes, at<void>(workspace, L.codes0), 8 * size_t(n), hipMemcpyDeviceToDevice,
+    if (codes && hipMemcpyAsync(codes, sort_input(workspace, L), 8 * size_t(n), hipMemcpyDeviceToDevice,
                                 stream) != hipSuccess)
         return BHTSNE_EDEVICE;
     launch_sort(n, Y, workspace, L, stream);

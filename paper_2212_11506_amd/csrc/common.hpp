@@ -21,6 +21,18 @@ constexpr int kSortTile = kSortBlock * kSortItems; // keys per tile
 // readers, so that the tiles' atomic adds spread over eight sets of addresses
 constexpr int kHistCopies = 8;
 constexpr int kHistWords = kSortPasses * (1 << kRadixBits);
+// How the codes of n points are sorted: by counting the smaller ones of all the
+// others, by a sample sort (one key in kSampleStride sampled, kSamplesPerBucket of
+// them a bucket), or by radix passes; k_sort.hip has the lines' measurements
+constexpr int kSampleStride = 64;
+constexpr int kSamplesPerBucket = 4;
+constexpr int64_t kRankSortMax = 8192;
+constexpr int64_t kSampleSortMax = int64_t(1) << 19; // 2048 buckets, whose splitters fit a block's LDS
+enum class SortMode { kRank, kSample, kRadix };
+inline SortMode sort_mode(int64_t n)
+{
+    return n <= kRankSortMax ? SortMode::kRank : n <= kSampleSortMax ? SortMode::kSample : SortMode::kRadix;
+}
 constexpr int kScanBlock = 256;
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanBlock * kScanItems;
@@ -187,6 +199,54 @@ inline Layout make_layout(int64_t n, int64_t nnz, int fbytes = 4, int dim = 2)
 template <typename T> __host__ __device__ inline T *at(void *ws, size_t off)
 {
     return reinterpret_cast<T *>(static_cast<char *>(ws) + off);
+}
+
+// where the keys that the sort reads are made (it leaves them in codes0 in order)
+inline uint64_t *sort_input(void *ws, const Layout &L)
+{
+    return at<uint64_t>(ws, sort_mode(L.n) == SortMode::kRank ? L.codes1 : L.codes0);
+}
+
+// Scratch of the sample sort, in the room of the tree's records and prefix sums
+// (both written after it)
+struct SampleSort {
+    int64_t samples, buckets;
+    uint64_t *code, *split;                    // sampled keys; the splitters' keys
+    uint32_t *split_idx, *count, *offset, *pos; // pos: a key's place in its bucket
+    uint16_t *bucket;                          // a key's bucket
+};
+
+inline SampleSort sample_sort(void *ws, const Layout &L)
+{
+    SampleSort s{};
+    s.samples = (L.n + kSampleStride - 1) / kSampleStride;
+    s.buckets = s.samples / kSamplesPerBucket > 1 ? s.samples / kSamplesPerBucket : 1;
+    s.code = at<uint64_t>(ws, L.nodes);
+    s.split = s.code + s.samples;
+    s.split_idx = reinterpret_cast<uint32_t *>(s.split + s.buckets);
+    s.count = s.split_idx + s.buckets;
+    s.offset = s.count + s.buckets;
+    s.pos = at<uint32_t>(ws, L.psum);
+    s.bucket = reinterpret_cast<uint16_t *>(s.pos + L.n);
+    return s;
+}
+
+// the position of sample j: one in each kSampleStride keys, at a place that
+// varies (a multiplicative hash), so that no period of the input hides from it
+__host__ __device__ inline int64_t sample_position(int64_t j, int64_t n)
+{
+    static_assert(kSampleStride == 64, "six bits of the hash");
+    const int64_t p = j * kSampleStride + ((uint32_t(j) * 2654435761u) >> 26);
+    return p < n ? p : n - 1;
+}
+
+// Called for every key i of the array to be sorted: keeps it if it is sampled
+// and clears the buckets' counters.
+__device__ inline void take_sample(int64_t i, uint64_t key, int64_t n, const SampleSort &s)
+{
+    const int64_t j = i / kSampleStride;
+    if (sample_position(j, n) == i) s.code[j] = key;
+    if (i < s.buckets) s.count[i] = 0;
 }
 
 // ---------------------------------------------------------------- wave64 helpers

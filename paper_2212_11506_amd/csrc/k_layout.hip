@@ -203,6 +203,13 @@ __global__ __launch_bounds__(kSortBlock) void keys_hist_kernel(const uint64_t *_
         if (sh[k]) atomicAdd(&hc[k], sh[k]);
 }
 
+// the sample sort's samples of existing keys
+__global__ __launch_bounds__(256) void keys_sample_kernel(const uint64_t *__restrict__ keys, int64_t n, SampleSort sample)
+{
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n) take_sample(i, keys[i], n, sample);
+}
+
 __global__ void sort_reset_kernel(Header *__restrict__ hdr, uint32_t *__restrict__ hist)
 {
     for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
@@ -1626,7 +1633,7 @@ static int relabel(const int64_t *row_ptr, const int32_t *col, const V *val, int
     const uint32_t *comp = at<uint32_t>(ws, L.split_b);
     const unsigned gn = unsigned((n + 255) / 256);
     const unsigned gw = unsigned((n + 3) / 4 < 65535 * 4 ? (n + 3) / 4 : 65535 * 4);
-    uint64_t *keys = at<uint64_t>(ws, L.codes0);
+    uint64_t *keys = sort_input(ws, L);
     if (order == kOrderBfs) {
         layout_keys_bfs_kernel<<<gn, 256, 0, st>>>(keys, comp, at<uint32_t>(ws, L.base), n);
     } else {
@@ -1644,8 +1651,11 @@ static int relabel(const int64_t *row_ptr, const int32_t *col, const V *val, int
         layout_keys_kernel<<<gn, 256, 0, st>>>(keys, comp, n, Y ? 1 : 0);
     }
     sort_reset_kernel<<<1, 256, 0, st>>>(hdr, at<uint32_t>(ws, L.hist));
-    keys_hist_kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(keys, n, at<uint32_t>(ws, L.hist),
-                                                                    at<uint32_t>(ws, L.status), L.sort_tiles);
+    if (sort_mode(n) == SortMode::kRadix)
+        keys_hist_kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(keys, n, at<uint32_t>(ws, L.hist),
+                                                                        at<uint32_t>(ws, L.status), L.sort_tiles);
+    else if (sort_mode(n) == SortMode::kSample)
+        keys_sample_kernel<<<gn, 256, 0, st>>>(keys, n, sample_sort(ws, L));
     // (the sorted copy of the points this also makes is not used)
     const V *ysrc = Y ? Y : reinterpret_cast<const V *>(at<char>(ws, L.ycopy));
     if constexpr (D == 3)

@@ -7,11 +7,23 @@
 // to each other, which is what the tree build and the repulsive traversal
 // rely on.
 //
-// The sort is an LSD radix sort over 8-bit digits (8 passes).  The global
-// digit histograms of all passes are accumulated while the codes are formed;
-// each pass is then a single kernel that ranks a tile in LDS, finds the
-// tile's global offsets with a decoupled look-back over the tiles before it,
-// and writes the tile out digit by digit.
+// The sort orders the pairs (code, index), which are distinct, so it need not be
+// stable.  Three ways, by the number of points:
+//  - up to kRankSortMax a key's place is counted, all against all, in one launch;
+//  - up to kSampleSortMax a sample sort: every 64th code, taken while the codes
+//    are formed, is ranked among the sampled ones, every fourth of those splits the
+//    pairs into buckets of about 256, and a key's place is counted in its bucket:
+//    four launches, each pair moved twice;
+//  - beyond, an LSD radix sort over 8-bit digits: eight passes, each a kernel that
+//    ranks a tile in LDS, finds the tile's global offsets with a decoupled
+//    look-back over the tiles before it, and writes the tile out digit by digit;
+//    its digit histograms are accumulated while the codes are formed.
+// A radix pass takes 9.5 us however few points there are (its look-back is a chain
+// of tiles), so eight of them are latency up to some 100k points; comparisons grow
+// with n, and faster.  us of the sort's kernels with the codes' and the box's, by
+// rank / sample / radix: 1500 points 16 / 32 / -, 3000 23 / 38 / 89, 8000 35 / 41 / -,
+// 10k 41 / 41 / 99, 70k - / 59 / 118, 300k - / 133 / 162, 600k - / 235 / 245, 1.3M
+// - / 545 / 430.  The lines lie where they meet.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -115,7 +127,8 @@ __global__ __launch_bounds__(256) void bbox_final_kernel(const T *__restrict__ p
         s[w][3] = mxy;
         sb[w] = anybad;
     }
-    for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
+    if (hist) // radix sort only
+        for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         T r[4] = {s[0][0], s[0][1], s[0][2], s[0][3]};
@@ -175,27 +188,49 @@ __device__ inline uint64_t spread_by_bytes(const uint16_t *__restrict__ tab, uin
            (uint64_t(tab[(v >> 16) & 0xffu]) << 32) | (uint64_t(tab[v >> 24]) << 48);
 }
 
+// The digit counts of a tile (radix sort): cleared with the tile's look-back
+// words of every pass, counted, and added to the global ones by the block.
+__device__ inline void clear_tile(uint32_t *sh, uint32_t *__restrict__ status, int64_t tiles)
+{
+    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock) {
+        sh[k] = 0;
+        status[(int64_t(k / kRadix) * tiles + blockIdx.x) * kRadix + k % kRadix] = 0;
+    }
+}
+
+__device__ inline void count_digits(uint32_t *sh, uint64_t code)
+{
+#pragma unroll
+    for (int p = 0; p < kSortPasses; ++p)
+        atomicAdd(&sh[p * kRadix + int((code >> (p * kRadixBits)) & (kRadix - 1))], 1u);
+}
+
+__device__ inline void add_digits(const uint32_t *sh, uint32_t *__restrict__ hist)
+{
+    __syncthreads();
+    uint32_t *hc = hist + (blockIdx.x % kHistCopies) * kHistWords;
+    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock)
+        if (sh[k]) atomicAdd(&hc[k], sh[k]);
+}
+
 // Codes of one tile of points, the private copy of Y (in the caller's order,
 // or in a layout order when `perm` is given: position i holds the point
 // perm[i], gathered, which costs less than scattering each point to its
-// position), the 8 global digit histograms; also clears the per-position tree
-// masks and this tile's look-back status words of every pass.
-template <typename T>
+// position), and what the sort wants: its samples (kRadix = false) or the 8 global
+// digit histograms and cleared look-back words of this tile; also clears the
+// per-position tree masks.
+template <typename T, bool kRadixSort>
 __global__ __launch_bounds__(kSortBlock) void morton_kernel(
     const vec2_t<T> *__restrict__ Y, int64_t n, const Header *__restrict__ hdr,
     uint64_t *__restrict__ codes, vec2_t<T> *__restrict__ ycopy, const uint32_t *__restrict__ perm,
-    uint32_t *__restrict__ hist, uint32_t *__restrict__ levelmask, uint32_t *__restrict__ status, int64_t tiles)
+    uint32_t *__restrict__ hist, uint32_t *__restrict__ levelmask, uint32_t *__restrict__ status, int64_t tiles,
+    SampleSort sample)
 {
-    __shared__ uint32_t sh[kSortPasses * kRadix];
+    __shared__ uint32_t sh[kRadixSort ? kSortPasses * kRadix : 1];
     __shared__ uint16_t s_spread[256];
     static_assert(kSortBlock == 256, "one spread-table entry per thread");
     s_spread[threadIdx.x] = uint16_t(spread_byte_rule(threadIdx.x));
-    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock) sh[k] = 0;
-    // clear this tile's look-back words of every pass
-    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock) {
-        int pass = k / kRadix, d = k % kRadix;
-        status[(int64_t(pass) * tiles + blockIdx.x) * kRadix + d] = 0;
-    }
+    if (kRadixSort) clear_tile(sh, status, tiles);
     __syncthreads();
     const double yr0 = hdr->yroot[0], yr1 = hdr->yroot[1], sc = hdr->scale;
     const int64_t base = int64_t(blockIdx.x) * kSortTile;
@@ -214,15 +249,13 @@ __global__ __launch_bounds__(kSortBlock) void morton_kernel(
                             (spread_by_bytes(s_spread, quantise(y.y, yr1, sc)) << 1);
             codes[i] = code;
             levelmask[i] = 0;
-#pragma unroll
-            for (int p = 0; p < kSortPasses; ++p)
-                atomicAdd(&sh[p * kRadix + int((code >> (p * kRadixBits)) & (kRadix - 1))], 1u);
+            if (kRadixSort)
+                count_digits(sh, code);
+            else if (sample.code)
+                take_sample(i, code, n, sample);
         }
     }
-    __syncthreads();
-    uint32_t *hc = hist + (blockIdx.x % kHistCopies) * kHistWords;
-    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock)
-        if (sh[k]) atomicAdd(&hc[k], sh[k]);
+    if (kRadixSort) add_digits(sh, hist);
 }
 
 // ------------------------------------------------------------------ 3-D box and codes
@@ -311,7 +344,8 @@ __global__ __launch_bounds__(256) void bbox3_final_kernel(const float *__restric
         }
         sb[w] = anybad;
     }
-    for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
+    if (hist) // radix sort only
+        for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t b = 0;
@@ -365,20 +399,17 @@ __device__ inline uint64_t spread3_by_bytes(const uint32_t *__restrict__ tab, ui
     return uint64_t(tab[v & 0xffu]) | (uint64_t(tab[(v >> 8) & 0xffu]) << 24) | (uint64_t(tab[v >> 16]) << 48);
 }
 
+template <bool kRadixSort>
 __global__ __launch_bounds__(kSortBlock) void morton3_kernel(
     const float3 *__restrict__ Y, int64_t n, const Header *__restrict__ hdr, uint64_t *__restrict__ codes,
     float3 *__restrict__ ycopy, const uint32_t *__restrict__ perm, uint32_t *__restrict__ hist,
-    uint32_t *__restrict__ levelmask, uint32_t *__restrict__ status, int64_t tiles)
+    uint32_t *__restrict__ levelmask, uint32_t *__restrict__ status, int64_t tiles, SampleSort sample)
 {
-    __shared__ uint32_t sh[kSortPasses * kRadix];
+    __shared__ uint32_t sh[kRadixSort ? kSortPasses * kRadix : 1];
     __shared__ uint32_t s_spread[256];
     static_assert(kSortBlock == 256, "one spread-table entry per thread");
     s_spread[threadIdx.x] = spread3_byte_rule(threadIdx.x);
-    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock) sh[k] = 0;
-    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock) {
-        const int pass = k / kRadix, d = k % kRadix;
-        status[(int64_t(pass) * tiles + blockIdx.x) * kRadix + d] = 0;
-    }
+    if (kRadixSort) clear_tile(sh, status, tiles);
     __syncthreads();
     const double yr0 = hdr->yroot[0], yr1 = hdr->yroot[1], yr2 = hdr->yroot[2], sc = hdr->scale;
     const int64_t base = int64_t(blockIdx.x) * kSortTile;
@@ -394,15 +425,13 @@ __global__ __launch_bounds__(kSortBlock) void morton3_kernel(
                                   (spread3_by_bytes(s_spread, quantise21(y.z, yr2, sc)) << 2);
             codes[i] = code;
             levelmask[i] = 0;
-#pragma unroll
-            for (int p = 0; p < kSortPasses; ++p)
-                atomicAdd(&sh[p * kRadix + int((code >> (p * kRadixBits)) & (kRadix - 1))], 1u);
+            if (kRadixSort)
+                count_digits(sh, code);
+            else if (sample.code)
+                take_sample(i, code, n, sample);
         }
     }
-    __syncthreads();
-    uint32_t *hc = hist + (blockIdx.x % kHistCopies) * kHistWords;
-    for (int k = threadIdx.x; k < kSortPasses * kRadix; k += kSortBlock)
-        if (sh[k]) atomicAdd(&hc[k], sh[k]);
+    if (kRadixSort) add_digits(sh, hist);
 }
 
 // ------------------------------------------------------------------ onesweep pass
@@ -584,7 +613,249 @@ __global__ __launch_bounds__(kSortBlock) void onesweep_kernel(
     }
 }
 
+// ------------------------------------------------------------------ ranks and sample sort
+// (code, index) order of two pairs
+__device__ inline bool pair_less(uint64_t ca, uint32_t ia, uint64_t cb, uint32_t ib)
+{
+    return ca < cb || (ca == cb && ia < ib);
+}
+
+// The number of pairs before the pair (code, ix) at position own + lane, counted by
+// the block's kWaves waves together, valid in wave 0.  own is a multiple of 64; what
+// lies below lo is before all 64 pairs, what lies from hi on after all of them.
+// idx null: a key's index is its position.  Every wave takes each kWaves-th run of
+// 64 keys, as scalar loads (addresses are uniform): three vector instructions a
+// comparison, no LDS and no barrier but the one of the sum.
+template <int kWaves, bool kIndexed>
+__device__ inline uint32_t pairs_before(const uint64_t *__restrict__ codes, const uint32_t *__restrict__ idx, uint32_t n,
+                                        uint32_t lo, uint32_t hi, uint32_t own, uint64_t code, uint32_t ix)
+{
+    __shared__ uint32_t s_count[kWaves][kWave];
+    const uint32_t w = uniform(threadIdx.x / kWave), lane = uint32_t(lane_id()), low = uint32_t(code);
+    auto index = [&](uint32_t k) { return kIndexed ? idx[k] : k; };
+    lo &= ~uint32_t(kWave - 1);
+    uint32_t r = 0;
+    for (uint32_t k0 = lo + w * kWave; k0 < hi; k0 += kWaves * kWave) {
+        if (k0 + kWave > n) {
+            for (uint32_t k = k0; k < n; ++k) r += pair_less(codes[k], index(k), code, ix) ? 1u : 0u;
+        } else if (k0 == own) {
+#pragma unroll 8
+            for (int k = 0; k < kWave; ++k) r += pair_less(codes[k0 + k], index(k0 + k), code, ix) ? 1u : 0u;
+        } else {
+            // equal codes are looked for by their low words and counted apart
+            bool tie = false;
+#pragma unroll
+            for (int k = 0; k < kWave; ++k) {
+                const uint64_t c = codes[k0 + k];
+                r += c < code ? 1u : 0u;
+                tie |= uint32_t(c) == low;
+            }
+            if (ballot(tie))
+                for (int k = 0; k < kWave; ++k) r += codes[k0 + k] == code && index(k0 + k) < ix ? 1u : 0u;
+        }
+    }
+    s_count[w][lane] = r;
+    __syncthreads();
+    if (w == 0) {
+        r += lo;
+#pragma unroll
+        for (int k = 1; k < kWaves; ++k) r += s_count[k][lane];
+    }
+    return r;
+}
+
+// All pairs in order, each key's place counted among all of them: n^2 comparisons,
+// spread over the chip.  2000 points: 8 us, where a bitonic sort in one block's LDS
+// took 28 and the eight radix passes 63.
+constexpr int kRankWaves = 16;
+
+template <typename V>
+__global__ __launch_bounds__(kRankWaves *kWave) void rank_sort_kernel(const uint64_t *__restrict__ codes, int64_t n,
+                                                                      uint64_t *__restrict__ keys,
+                                                                      uint32_t *__restrict__ idx,
+                                                                      const V *__restrict__ ysrc, V *__restrict__ ys)
+{
+    const uint32_t own = blockIdx.x * kWave, x = own + uint32_t(lane_id());
+    const bool live = int64_t(x) < n;
+    const uint64_t code = live ? codes[x] : 0;
+    const uint32_t r = pairs_before<kRankWaves, false>(codes, nullptr, uint32_t(n), 0, uint32_t(n), own, code, x);
+    if (threadIdx.x >= kWave || !live || int64_t(r) >= n) return;
+    keys[r] = code;
+    idx[r] = x;
+    ys[r] = ysrc[x];
+}
+
+// Waits until the block's global atomics are done (they take effect where every
+// XCD sees them, and the last block reads them back with atomic loads), so that
+// the ticket drawn after it counts them; a fence would write back the whole L2.
+__device__ inline void adds_done()
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
+// 1. The splitters: every kSamplesPerBucket-th of the sampled keys in order (their
+// indices increase with their positions).
+__global__ __launch_bounds__(kRankWaves *kWave) void sample_split_kernel(const uint64_t *__restrict__ code, SampleSort s,
+                                                                         int64_t n)
+{
+    const uint32_t own = blockIdx.x * kWave, x = own + uint32_t(lane_id());
+    const bool live = int64_t(x) < s.samples;
+    const uint64_t c = live ? code[x] : 0;
+    const uint32_t r = pairs_before<kRankWaves, false>(code, nullptr, uint32_t(s.samples), 0, uint32_t(s.samples), own, c, x);
+    if (threadIdx.x >= kWave || !live) return;
+    const uint32_t b = r / kSamplesPerBucket;
+    if (r % kSamplesPerBucket == kSamplesPerBucket - 1 && int64_t(b) < s.buckets - 1) {
+        s.split[b] = c;
+        s.split_idx[b] = uint32_t(sample_position(x, n));
+    }
+}
+
+// 2. Every key's bucket, the number of splitters at or below it (binary search
+// in LDS), and its place in the bucket: a tile counts its keys per bucket in LDS
+// and takes its places from the buckets' counters, in any order (the buckets are
+// sorted afterwards).  The last block turns the counts into offsets.
+constexpr int kBucketBlock = 1024, kBucketItems = 4;
+constexpr int kBucketTile = kBucketBlock * kBucketItems;
+
+__global__ __launch_bounds__(kBucketBlock) void sample_bucket_kernel(const uint64_t *__restrict__ codes, int64_t n,
+                                                                     SampleSort s, Header *__restrict__ hdr)
+{
+    extern __shared__ uint64_t s_mem[]; // splitters' keys, their indices, the tile's counts
+    const int splits = int(s.buckets) - 1;
+    uint64_t *s_code = s_mem;
+    uint32_t *s_idx = reinterpret_cast<uint32_t *>(s_code + s.buckets), *s_cnt = s_idx + s.buckets;
+    __shared__ bool s_last;
+    __shared__ uint32_t s_wave[kBucketBlock / kWave];
+    for (int k = threadIdx.x; k < int(s.buckets); k += kBucketBlock) {
+        if (k < splits) {
+            s_code[k] = s.split[k];
+            s_idx[k] = s.split_idx[k];
+        }
+        s_cnt[k] = 0;
+    }
+    __syncthreads();
+    const int64_t base = int64_t(blockIdx.x) * kBucketTile + threadIdx.x;
+    uint64_t key[kBucketItems];
+    uint32_t at_or_below[kBucketItems], local[kBucketItems];
+#pragma unroll
+    for (int q = 0; q < kBucketItems; ++q) {
+        const int64_t i = base + q * kBucketBlock;
+        key[q] = i < n ? codes[i] : 0;
+        at_or_below[q] = 0;
+    }
+    int top = 1;
+    while (2 * top <= splits) top *= 2;
+    for (int w = top; w > 0; w >>= 1) {
+#pragma unroll
+        for (int q = 0; q < kBucketItems; ++q) {
+            const int k = int(at_or_below[q]) + w - 1; // the splitter that decides on this step
+            if (k < splits && !pair_less(key[q], uint32_t(base + q * kBucketBlock), s_code[k], s_idx[k]))
+                at_or_below[q] += uint32_t(w);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kBucketItems; ++q)
+        local[q] = base + q * kBucketBlock < n ? atomicAdd(&s_cnt[at_or_below[q]], 1u) : 0u;
+    __syncthreads();
+    for (int k = threadIdx.x; k < int(s.buckets); k += kBucketBlock)
+        if (s_cnt[k]) s_cnt[k] = atomicAdd(&s.count[k], s_cnt[k]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kBucketItems; ++q) {
+        const int64_t i = base + q * kBucketBlock;
+        if (i < n) {
+            s.bucket[i] = uint16_t(at_or_below[q]);
+            s.pos[i] = s_cnt[at_or_below[q]] + local[q];
+        }
+    }
+    adds_done();
+    if (threadIdx.x == 0) s_last = atomicAdd(&hdr->tile_counter[0], 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    // exclusive scan of the counts, a contiguous run a thread
+    const int per = (int(s.buckets) + kBucketBlock - 1) / kBucketBlock, first = int(threadIdx.x) * per;
+    uint32_t sum = 0;
+    for (int k = first; k < first + per && k < int(s.buckets); ++k) sum += s_cnt[k] = peek(&s.count[k]);
+    uint32_t x = sum;
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) s_wave[wave] = x;
+    __syncthreads();
+    uint32_t run = x - sum;
+    for (int k = 0; k < wave; ++k) run += s_wave[k];
+    for (int k = first; k < first + per && k < int(s.buckets); ++k) {
+        s.offset[k] = run;
+        run += s_cnt[k];
+    }
+    if (threadIdx.x == 0) s.offset[s.buckets] = uint32_t(n);
+}
+
+// 3. The pairs to their buckets.
+__global__ __launch_bounds__(256) void sample_scatter_kernel(const uint64_t *__restrict__ codes, int64_t n,
+                                                             SampleSort s, uint64_t *__restrict__ keys_out,
+                                                             uint32_t *__restrict__ idx_out)
+{
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t o = s.offset[s.bucket[i]] + s.pos[i];
+    if (o < uint32_t(n)) {
+        keys_out[o] = codes[i];
+        idx_out[o] = uint32_t(i);
+    }
+}
+
+// The bucket that position x lies in: 64 offsets are looked at at a time.
+__device__ inline uint32_t bucket_of(const uint32_t *__restrict__ offset, uint32_t buckets, uint32_t x)
+{
+    uint32_t lo = 0, hi = buckets;
+    while (hi - lo > 1) {
+        const uint32_t step = (hi - lo + kWave - 1) / kWave, k = lo + uint32_t(lane_id()) * step;
+        const uint32_t c = uint32_t(__popcll(ballot(k < hi && offset[k] <= x)));
+        lo += (c ? c - 1 : 0) * step;
+        hi = lo + step < hi ? lo + step : hi;
+    }
+    return lo;
+}
+
+// 4. The pairs in order: 64 of them a block, each counted among the buckets that
+// any of the 64 lies in (what is before those is before all of them): about 400
+// comparisons a key, 1.6 times the mean bucket.  No bucket is too large: one that
+// held all of the 2^19 points, which the sample's places make unlikely for any
+// input, would cost some 40 ms.  70k points: 16 us; the buckets sorted by bitonic
+// networks in LDS, a block each, took 53, by runs of 64 merged in LDS 60.
+constexpr int kPlaceWaves = 4;
+
+template <typename V>
+__global__ __launch_bounds__(kPlaceWaves *kWave) void bucket_sort_kernel(
+    const uint64_t *__restrict__ keys_in, const uint32_t *__restrict__ idx_in, const uint32_t *__restrict__ offset,
+    uint32_t buckets, int64_t n, uint64_t *__restrict__ keys, uint32_t *__restrict__ idx, const V *__restrict__ ysrc,
+    V *__restrict__ ys)
+{
+    const uint32_t own = blockIdx.x * kWave, x = own + uint32_t(lane_id());
+    const bool live = int64_t(x) < n;
+    const uint64_t code = live ? keys_in[x] : 0;
+    const uint32_t ix = live ? idx_in[x] : 0;
+    const uint32_t last = int64_t(own) + kWave <= n ? own + kWave - 1 : uint32_t(n - 1);
+    const uint32_t lo = uniform(offset[bucket_of(offset, buckets, own)]);
+    const uint32_t hi = uniform(offset[bucket_of(offset, buckets, last) + 1]);
+    const uint32_t r = pairs_before<kPlaceWaves, true>(keys_in, idx_in, uint32_t(n), lo, hi, own, code, ix);
+    if (threadIdx.x >= kWave || !live || int64_t(r) >= n) return;
+    keys[r] = code;
+    idx[r] = ix;
+    ys[r] = ix < uint32_t(n) ? ysrc[ix] : V{};
+}
+
 // ------------------------------------------------------------------ launchers
+static SampleSort samples_of(int64_t n, void *ws, const Layout &L)
+{
+    return sort_mode(n) == SortMode::kSample ? sample_sort(ws, L) : SampleSort{};
+}
+
 template <typename T> void launch_bbox(const T *Y, int64_t n, void *ws, const Layout &L, hipStream_t st)
 {
     int blocks = int((n + 255) / 256);
@@ -592,7 +863,7 @@ template <typename T> void launch_bbox(const T *Y, int64_t n, void *ws, const La
     bbox_partial_kernel<T><<<blocks, 256, 0, st>>>(reinterpret_cast<const vec2_t<T> *>(Y), n,
                                                    at<T>(ws, L.bbox_part));
     bbox_final_kernel<T><<<1, 256, 0, st>>>(at<T>(ws, L.bbox_part), blocks, at<Header>(ws, L.header),
-                                            at<uint32_t>(ws, L.hist));
+                                            sort_mode(n) == SortMode::kRadix ? at<uint32_t>(ws, L.hist) : nullptr);
 }
 template void launch_bbox<float>(const float *, int64_t, void *, const Layout &, hipStream_t);
 template void launch_bbox<double>(const double *, int64_t, void *, const Layout &, hipStream_t);
@@ -603,20 +874,24 @@ void launch_bbox_morton3(const float *Y, int64_t n, const uint32_t *perm, void *
     if (blocks > kBBoxBlocks) blocks = kBBoxBlocks;
     const float3 *y3 = reinterpret_cast<const float3 *>(Y);
     bbox3_partial_kernel<<<blocks, 256, 0, st>>>(y3, n, at<float>(ws, L.bbox_part));
+    const bool radix = sort_mode(n) == SortMode::kRadix;
     bbox3_final_kernel<<<1, 256, 0, st>>>(at<float>(ws, L.bbox_part), blocks, at<Header>(ws, L.header),
-                                          at<uint32_t>(ws, L.hist));
-    morton3_kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(
-        y3, n, at<Header>(ws, L.header), at<uint64_t>(ws, L.codes0), at<float3>(ws, L.ycopy), perm,
-        at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask), at<uint32_t>(ws, L.status), L.sort_tiles);
+                                          radix ? at<uint32_t>(ws, L.hist) : nullptr);
+    auto *kernel = radix ? morton3_kernel<true> : morton3_kernel<false>;
+    kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(
+        y3, n, at<Header>(ws, L.header), sort_input(ws, L), at<float3>(ws, L.ycopy), perm,
+        at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask), at<uint32_t>(ws, L.status), L.sort_tiles,
+        samples_of(n, ws, L));
 }
 
 template <typename T>
 void launch_morton(const T *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L, hipStream_t st)
 {
-    morton_kernel<T><<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(
-        reinterpret_cast<const vec2_t<T> *>(Y), n, at<Header>(ws, L.header), at<uint64_t>(ws, L.codes0),
+    auto *kernel = sort_mode(n) == SortMode::kRadix ? morton_kernel<T, true> : morton_kernel<T, false>;
+    kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(
+        reinterpret_cast<const vec2_t<T> *>(Y), n, at<Header>(ws, L.header), sort_input(ws, L),
         at<vec2_t<T>>(ws, L.ycopy), perm, at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask),
-        at<uint32_t>(ws, L.status), L.sort_tiles);
+        at<uint32_t>(ws, L.status), L.sort_tiles, samples_of(n, ws, L));
 }
 template void launch_morton<float>(const float *, int64_t, const uint32_t *, void *, const Layout &, hipStream_t);
 template void launch_morton<double>(const double *, int64_t, const uint32_t *, void *, const Layout &,
@@ -631,6 +906,21 @@ template <typename V> void launch_sort_points(int64_t n, const V *ysrc, void *ws
     Header *hdr = at<Header>(ws, L.header);
     const uint32_t *hist = at<uint32_t>(ws, L.hist);
     V *ys = at<V>(ws, L.ys);
+    const unsigned groups = unsigned((n + kWave - 1) / kWave);
+    if (sort_mode(n) == SortMode::kRank) {
+        rank_sort_kernel<V><<<groups, kRankWaves * kWave, 0, st>>>(k[1], n, k[0], x[0], ysrc, ys);
+        return;
+    }
+    if (sort_mode(n) == SortMode::kSample) {
+        const SampleSort s = sample_sort(ws, L);
+        sample_split_kernel<<<unsigned((s.samples + kWave - 1) / kWave), kRankWaves * kWave, 0, st>>>(s.code, s, n);
+        sample_bucket_kernel<<<unsigned((n + kBucketTile - 1) / kBucketTile), kBucketBlock, size_t(s.buckets) * 16,
+                               st>>>(k[0], n, s, hdr);
+        sample_scatter_kernel<<<unsigned((n + 255) / 256), 256, 0, st>>>(k[0], n, s, k[1], x[1]);
+        bucket_sort_kernel<V><<<groups, kPlaceWaves * kWave, 0, st>>>(k[1], x[1], s.offset, uint32_t(s.buckets), n, k[0],
+                                                                     x[0], ysrc, ys);
+        return;
+    }
     for (int p = 0; p < kSortPasses; ++p) {
         uint32_t *status = at<uint32_t>(ws, L.status) + int64_t(p) * L.sort_tiles * kRadix;
         int src = p & 1, dst = src ^ 1;
