@@ -20,12 +20,13 @@
 //    its digit histograms are accumulated while the codes are formed.
 // A radix pass takes 9.5 us however few points there are (its look-back is a chain
 // of tiles), so eight of them are latency up to some 100k points; comparisons grow
-// with n, and faster.  us of the sort's kernels with the codes' and the box's, by
-// rank / sample / radix: 1500 points 16 / 32 / -, 3000 23 / 38 / 89, 8000 35 / 41 / -,
-// 10k 41 / 41 / 99, 70k - / 59 / 118, 300k - / 133 / 162, 600k - / 235 / 245, 1.3M
-// - / 545 / 430.  The lines lie where they meet.
+// with n, and faster.  us of the kernels that make the codes and sort them, by
+// rank / sample / radix: 1500 points 11 / 27 / -, 3000 16 / 33 / 89, 8000 27 / 32 / -,
+// 10k 32 / 31 / 99, 70k - / 48 / 118, 300k - / 124 / 162, 600k - / 227 / 245, 1.3M
+// - / 535 / 430.  The lines lie where they meet.
 #include "common.hpp"
 #include "kernels.hpp"
+#include <algorithm>
 
 namespace bht {
 
@@ -95,12 +96,12 @@ __device__ inline void reset_call_state(Header *hdr, uint32_t nonfinite)
     hdr->max_depth = 0;
 }
 
-// One block: finish the box, derive the quantisation parameters in fp64 and
-// reset the per-call counters and histograms.
+// The box from its parts by a block of 256 threads, and from it the quantisation
+// parameters in fp64: s_root = {root of either axis, scale}.  `write`: leave them
+// in the header as well and reset the per-call counters.
 template <typename T>
-__global__ __launch_bounds__(256) void bbox_final_kernel(const T *__restrict__ part, int nparts,
-                                                         Header *__restrict__ hdr,
-                                                         uint32_t *__restrict__ hist)
+__device__ inline void finish_box(const T *__restrict__ part, int nparts, Header *__restrict__ hdr, bool write,
+                                  double *s_root)
 {
     T mnx = INFINITY, mny = INFINITY, mxx = -INFINITY, mxy = -INFINITY;
     uint32_t bad = 0;
@@ -127,8 +128,6 @@ __global__ __launch_bounds__(256) void bbox_final_kernel(const T *__restrict__ p
         s[w][3] = mxy;
         sb[w] = anybad;
     }
-    if (hist) // radix sort only
-        for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         T r[4] = {s[0][0], s[0][1], s[0][2], s[0][3]};
@@ -140,24 +139,40 @@ __global__ __launch_bounds__(256) void bbox_final_kernel(const T *__restrict__ p
             r[3] = vmax(r[3], s[k][3]);
             b |= sb[k];
         }
-        hdr->bmin[0] = float(r[0]);
-        hdr->bmax[0] = float(r[1]);
-        hdr->bmin[1] = float(r[2]);
-        hdr->bmax[1] = float(r[3]);
         // fp64, fixed operation order: the codes depend on these bits
         double c0 = (double(r[0]) + double(r[1])) * 0.5;
         double c1 = (double(r[2]) + double(r[3])) * 0.5;
         double e0 = double(r[1]) - double(r[0]);
         double e1 = double(r[3]) - double(r[2]);
         double rs = 0.5 * (e0 > e1 ? e0 : e1);
-        hdr->cent[0] = c0;
-        hdr->cent[1] = c1;
-        hdr->rspan = rs;
-        hdr->yroot[0] = c0 - rs;
-        hdr->yroot[1] = c1 - rs;
-        hdr->scale = rs > 0.0 ? 2147483648.0 / rs : 0.0;
-        reset_call_state(hdr, b);
+        s_root[0] = c0 - rs;
+        s_root[1] = c1 - rs;
+        s_root[2] = rs > 0.0 ? 2147483648.0 / rs : 0.0;
+        if (write) {
+            hdr->bmin[0] = float(r[0]);
+            hdr->bmax[0] = float(r[1]);
+            hdr->bmin[1] = float(r[2]);
+            hdr->bmax[1] = float(r[3]);
+            hdr->cent[0] = c0;
+            hdr->cent[1] = c1;
+            hdr->rspan = rs;
+            hdr->yroot[0] = c0 - rs;
+            hdr->yroot[1] = c1 - rs;
+            hdr->scale = s_root[2];
+            reset_call_state(hdr, b);
+        }
     }
+    __syncthreads();
+}
+
+// One block: the box and the histograms' clearing, before the radix sort's codes.
+template <typename T>
+__global__ __launch_bounds__(256) void bbox_final_kernel(const T *__restrict__ part, int nparts,
+                                                         Header *__restrict__ hdr, uint32_t *__restrict__ hist)
+{
+    __shared__ double s_root[3];
+    for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
+    finish_box(part, nparts, hdr, true, s_root);
 }
 
 // ------------------------------------------------------------------ Morton
@@ -216,26 +231,37 @@ __device__ inline void add_digits(const uint32_t *sh, uint32_t *__restrict__ his
 // Codes of one tile of points, the private copy of Y (in the caller's order,
 // or in a layout order when `perm` is given: position i holds the point
 // perm[i], gathered, which costs less than scattering each point to its
-// position), and what the sort wants: its samples (kRadix = false) or the 8 global
-// digit histograms and cleared look-back words of this tile; also clears the
-// per-position tree masks.
+// position), and what the sort wants: its samples (kRadixSort = false) or the 8
+// global digit histograms and cleared look-back words of this tile; also clears the
+// per-position tree masks.  Without the radix sort every block finishes the box for
+// itself (2-4 us of a launch for at most 16 KB read again) and takes one point a
+// thread: eight, the radix sort's tile, leave 70k points in 35 blocks.  70k points: the
+// box's last launch and this one took 5.4 + 10.8 us, now 4.8; 1500 points 2.9 + 7.0, now
+// 4.1.
 template <typename T, bool kRadixSort>
 __global__ __launch_bounds__(kSortBlock) void morton_kernel(
-    const vec2_t<T> *__restrict__ Y, int64_t n, const Header *__restrict__ hdr,
+    const vec2_t<T> *__restrict__ Y, int64_t n, const T *__restrict__ part, int nparts, Header *__restrict__ hdr,
     uint64_t *__restrict__ codes, vec2_t<T> *__restrict__ ycopy, const uint32_t *__restrict__ perm,
     uint32_t *__restrict__ hist, uint32_t *__restrict__ levelmask, uint32_t *__restrict__ status, int64_t tiles,
     SampleSort sample)
 {
     __shared__ uint32_t sh[kRadixSort ? kSortPasses * kRadix : 1];
     __shared__ uint16_t s_spread[256];
+    __shared__ double s_root[3];
     static_assert(kSortBlock == 256, "one spread-table entry per thread");
     s_spread[threadIdx.x] = uint16_t(spread_byte_rule(threadIdx.x));
-    if (kRadixSort) clear_tile(sh, status, tiles);
-    __syncthreads();
-    const double yr0 = hdr->yroot[0], yr1 = hdr->yroot[1], sc = hdr->scale;
-    const int64_t base = int64_t(blockIdx.x) * kSortTile;
+    if (kRadixSort) {
+        clear_tile(sh, status, tiles);
+        __syncthreads();
+    } else {
+        finish_box(part, nparts, hdr, blockIdx.x == 0, s_root);
+    }
+    const double yr0 = kRadixSort ? hdr->yroot[0] : s_root[0], yr1 = kRadixSort ? hdr->yroot[1] : s_root[1];
+    const double sc = kRadixSort ? hdr->scale : s_root[2];
+    constexpr int kItems = kRadixSort ? kSortItems : 1;
+    const int64_t base = int64_t(blockIdx.x) * kItems * kSortBlock;
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < kItems; ++r) {
         int64_t i = base + r * kSortBlock + threadIdx.x;
         if (i < n) {
             const vec2_t<T> y = Y[i];
@@ -313,8 +339,9 @@ __global__ __launch_bounds__(256) void bbox3_partial_kernel(const float3 *__rest
     }
 }
 
-__global__ __launch_bounds__(256) void bbox3_final_kernel(const float *__restrict__ part, int nparts,
-                                                          Header *__restrict__ hdr, uint32_t *__restrict__ hist)
+// finish_box for a 3-D embedding: s_root = {root of each axis, scale}
+__device__ inline void finish_box3(const float *__restrict__ part, int nparts, Header *__restrict__ hdr, bool write,
+                                   double *s_root)
 {
     float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
     uint32_t bad = 0;
@@ -344,8 +371,6 @@ __global__ __launch_bounds__(256) void bbox3_final_kernel(const float *__restric
         }
         sb[w] = anybad;
     }
-    if (hist) // radix sort only
-        for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t b = 0;
@@ -357,22 +382,37 @@ __global__ __launch_bounds__(256) void bbox3_final_kernel(const float *__restric
                 lo = fminf(lo, s[k][2 * d]);
                 hi = fmaxf(hi, s[k][2 * d + 1]);
             }
-            hdr->bmin[d] = lo;
-            hdr->bmax[d] = hi;
+            if (write) {
+                hdr->bmin[d] = lo;
+                hdr->bmax[d] = hi;
+            }
             // fp64, fixed operation order: the codes depend on these bits
             c[d] = (double(lo) + double(hi)) * 0.5;
             const double ext = double(hi) - double(lo);
             widest = ext > widest ? ext : widest;
         }
         const double rs = 0.5 * widest;
-        for (int d = 0; d < 3; ++d) {
-            hdr->cent[d] = c[d];
-            hdr->yroot[d] = c[d] - rs;
+        for (int d = 0; d < 3; ++d) s_root[d] = c[d] - rs;
+        s_root[3] = rs > 0.0 ? 1048576.0 / rs : 0.0;
+        if (write) {
+            for (int d = 0; d < 3; ++d) {
+                hdr->cent[d] = c[d];
+                hdr->yroot[d] = s_root[d];
+            }
+            hdr->rspan = rs;
+            hdr->scale = s_root[3];
+            reset_call_state(hdr, b);
         }
-        hdr->rspan = rs;
-        hdr->scale = rs > 0.0 ? 1048576.0 / rs : 0.0;
-        reset_call_state(hdr, b);
     }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void bbox3_final_kernel(const float *__restrict__ part, int nparts,
+                                                          Header *__restrict__ hdr, uint32_t *__restrict__ hist)
+{
+    __shared__ double s_root[4];
+    for (int k = threadIdx.x; k < kHistCopies * kHistWords; k += blockDim.x) hist[k] = 0;
+    finish_box3(part, nparts, hdr, true, s_root);
 }
 
 __device__ inline uint32_t quantise21(float y, double yroot, double scale)
@@ -401,20 +441,27 @@ __device__ inline uint64_t spread3_by_bytes(const uint32_t *__restrict__ tab, ui
 
 template <bool kRadixSort>
 __global__ __launch_bounds__(kSortBlock) void morton3_kernel(
-    const float3 *__restrict__ Y, int64_t n, const Header *__restrict__ hdr, uint64_t *__restrict__ codes,
-    float3 *__restrict__ ycopy, const uint32_t *__restrict__ perm, uint32_t *__restrict__ hist,
+    const float3 *__restrict__ Y, int64_t n, const float *__restrict__ part, int nparts, Header *__restrict__ hdr,
+    uint64_t *__restrict__ codes, float3 *__restrict__ ycopy, const uint32_t *__restrict__ perm, uint32_t *__restrict__ hist,
     uint32_t *__restrict__ levelmask, uint32_t *__restrict__ status, int64_t tiles, SampleSort sample)
 {
     __shared__ uint32_t sh[kRadixSort ? kSortPasses * kRadix : 1];
     __shared__ uint32_t s_spread[256];
+    __shared__ double s_root[4];
     static_assert(kSortBlock == 256, "one spread-table entry per thread");
     s_spread[threadIdx.x] = spread3_byte_rule(threadIdx.x);
-    if (kRadixSort) clear_tile(sh, status, tiles);
-    __syncthreads();
-    const double yr0 = hdr->yroot[0], yr1 = hdr->yroot[1], yr2 = hdr->yroot[2], sc = hdr->scale;
-    const int64_t base = int64_t(blockIdx.x) * kSortTile;
+    if (kRadixSort) {
+        clear_tile(sh, status, tiles);
+        __syncthreads();
+    } else {
+        finish_box3(part, nparts, hdr, blockIdx.x == 0, s_root);
+    }
+    const double yr0 = kRadixSort ? hdr->yroot[0] : s_root[0], yr1 = kRadixSort ? hdr->yroot[1] : s_root[1];
+    const double yr2 = kRadixSort ? hdr->yroot[2] : s_root[2], sc = kRadixSort ? hdr->scale : s_root[3];
+    constexpr int kItems = kRadixSort ? kSortItems : 1;
+    const int64_t base = int64_t(blockIdx.x) * kItems * kSortBlock;
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < kItems; ++r) {
         const int64_t i = base + r * kSortBlock + threadIdx.x;
         if (i < n) {
             const float3 y = Y[i];
@@ -856,41 +903,47 @@ static SampleSort samples_of(int64_t n, void *ws, const Layout &L)
     return sort_mode(n) == SortMode::kSample ? sample_sort(ws, L) : SampleSort{};
 }
 
+static int box_parts(int64_t n) { return int(std::min<int64_t>((n + 255) / 256, kBBoxBlocks)); }
+
+// blocks of the kernels that make the codes: the radix sort's tiles, or a point a thread
+static unsigned code_blocks(int64_t n, const Layout &L)
+{
+    return unsigned(sort_mode(n) == SortMode::kRadix ? L.sort_tiles : (n + kSortBlock - 1) / kSortBlock);
+}
+
 template <typename T> void launch_bbox(const T *Y, int64_t n, void *ws, const Layout &L, hipStream_t st)
 {
-    int blocks = int((n + 255) / 256);
-    if (blocks > kBBoxBlocks) blocks = kBBoxBlocks;
-    bbox_partial_kernel<T><<<blocks, 256, 0, st>>>(reinterpret_cast<const vec2_t<T> *>(Y), n,
-                                                   at<T>(ws, L.bbox_part));
-    bbox_final_kernel<T><<<1, 256, 0, st>>>(at<T>(ws, L.bbox_part), blocks, at<Header>(ws, L.header),
-                                            sort_mode(n) == SortMode::kRadix ? at<uint32_t>(ws, L.hist) : nullptr);
+    bbox_partial_kernel<T><<<box_parts(n), 256, 0, st>>>(reinterpret_cast<const vec2_t<T> *>(Y), n,
+                                                         at<T>(ws, L.bbox_part));
+    if (sort_mode(n) == SortMode::kRadix)
+        bbox_final_kernel<T><<<1, 256, 0, st>>>(at<T>(ws, L.bbox_part), box_parts(n), at<Header>(ws, L.header),
+                                                at<uint32_t>(ws, L.hist));
 }
 template void launch_bbox<float>(const float *, int64_t, void *, const Layout &, hipStream_t);
 template void launch_bbox<double>(const double *, int64_t, void *, const Layout &, hipStream_t);
 
 void launch_bbox_morton3(const float *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L, hipStream_t st)
 {
-    int blocks = int((n + 255) / 256);
-    if (blocks > kBBoxBlocks) blocks = kBBoxBlocks;
     const float3 *y3 = reinterpret_cast<const float3 *>(Y);
-    bbox3_partial_kernel<<<blocks, 256, 0, st>>>(y3, n, at<float>(ws, L.bbox_part));
+    bbox3_partial_kernel<<<box_parts(n), 256, 0, st>>>(y3, n, at<float>(ws, L.bbox_part));
     const bool radix = sort_mode(n) == SortMode::kRadix;
-    bbox3_final_kernel<<<1, 256, 0, st>>>(at<float>(ws, L.bbox_part), blocks, at<Header>(ws, L.header),
-                                          radix ? at<uint32_t>(ws, L.hist) : nullptr);
+    if (radix)
+        bbox3_final_kernel<<<1, 256, 0, st>>>(at<float>(ws, L.bbox_part), box_parts(n), at<Header>(ws, L.header),
+                                              at<uint32_t>(ws, L.hist));
     auto *kernel = radix ? morton3_kernel<true> : morton3_kernel<false>;
-    kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(
-        y3, n, at<Header>(ws, L.header), sort_input(ws, L), at<float3>(ws, L.ycopy), perm,
-        at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask), at<uint32_t>(ws, L.status), L.sort_tiles,
-        samples_of(n, ws, L));
+    kernel<<<code_blocks(n, L), kSortBlock, 0, st>>>(
+        y3, n, at<float>(ws, L.bbox_part), box_parts(n), at<Header>(ws, L.header), sort_input(ws, L),
+        at<float3>(ws, L.ycopy), perm, at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask),
+        at<uint32_t>(ws, L.status), L.sort_tiles, samples_of(n, ws, L));
 }
 
 template <typename T>
 void launch_morton(const T *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L, hipStream_t st)
 {
     auto *kernel = sort_mode(n) == SortMode::kRadix ? morton_kernel<T, true> : morton_kernel<T, false>;
-    kernel<<<unsigned(L.sort_tiles), kSortBlock, 0, st>>>(
-        reinterpret_cast<const vec2_t<T> *>(Y), n, at<Header>(ws, L.header), sort_input(ws, L),
-        at<vec2_t<T>>(ws, L.ycopy), perm, at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask),
+    kernel<<<code_blocks(n, L), kSortBlock, 0, st>>>(
+        reinterpret_cast<const vec2_t<T> *>(Y), n, at<T>(ws, L.bbox_part), box_parts(n), at<Header>(ws, L.header),
+        sort_input(ws, L), at<vec2_t<T>>(ws, L.ycopy), perm, at<uint32_t>(ws, L.hist), at<uint32_t>(ws, L.levelmask),
         at<uint32_t>(ws, L.status), L.sort_tiles, samples_of(n, ws, L));
 }
 template void launch_morton<float>(const float *, int64_t, const uint32_t *, void *, const Layout &, hipStream_t);

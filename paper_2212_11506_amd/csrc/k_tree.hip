@@ -354,7 +354,8 @@ __global__ __launch_bounds__(kScanBlock) void scan_reduce_kernel(
     }
 }
 
-// one block: exclusive scan over the tile totals, in place; totals -> base[n], psum[n]
+// One block: exclusive scan over the tile totals, in place; totals -> base[n], psum[n].
+// Up to kScanBlock tiles every block of scan_down_kernel does it for itself instead.
 template <int D>
 __global__ __launch_bounds__(kScanBlock) void scan_top_kernel(uint32_t *__restrict__ tile_cnt,
                                                               double *__restrict__ tile_sum, int64_t tiles,
@@ -397,14 +398,36 @@ __global__ __launch_bounds__(kScanBlock) void scan_top_kernel(uint32_t *__restri
     }
 }
 
-template <int D, typename T>
+// kTop: the tile totals are not scanned yet and at most kScanBlock.  Each block
+// scans them, one a thread, in the order of scan_top_kernel (which takes one a
+// thread too at such counts), so that the sums are the same to the last bit.  70k
+// points: 4.3 us for that kernel and 4.8 for this one before, 5.4 now.
+template <int D, typename T, bool kTop>
 __global__ __launch_bounds__(kScanBlock) void scan_down_kernel(
     const uint64_t *__restrict__ codes, const uint32_t *__restrict__ levelmask,
-    const point_t<D, T> *__restrict__ ys, const Header *__restrict__ hdr, int64_t n,
+    const point_t<D, T> *__restrict__ ys, Header *__restrict__ hdr, int64_t n,
     const uint32_t *__restrict__ tile_cnt, const double *__restrict__ tile_sum,
     uint32_t *__restrict__ base, double *__restrict__ psum)
 {
-    __shared__ ScanVal<D> s_wave[4];
+    __shared__ ScanVal<D> s_wave[4], s_top[5]; // s_top: the waves' totals and this tile's offset
+    if (kTop) {
+        const bool in = threadIdx.x < gridDim.x;
+        ScanVal<D> v = scan_zero<D>(), all;
+        if (in) {
+            v.c = tile_cnt[threadIdx.x];
+#pragma unroll
+            for (int d = 0; d < D; ++d) v.s[d] = tile_sum[int64_t(threadIdx.x) * D + d];
+            v = scan_add(scan_zero<D>(), v);
+        }
+        const ScanVal<D> before = block_scan_excl(v, s_top, &all);
+        if (threadIdx.x == blockIdx.x) s_top[4] = before;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            base[n] = all.c;
+#pragma unroll
+            for (int d = 0; d < D; ++d) psum[n * D + d] = all.s[d];
+            hdr->nodes = all.c;
+        }
+    }
     double c[D];
     load_centre<D>(hdr, c);
     int64_t first = int64_t(blockIdx.x) * kScanTile + int64_t(threadIdx.x) * kScanItems;
@@ -419,9 +442,13 @@ __global__ __launch_bounds__(kScanBlock) void scan_down_kernel(
     ScanVal<D> tot;
     ScanVal<D> run = block_scan_excl(acc, s_wave, &tot);
     ScanVal<D> tile_off;
-    tile_off.c = tile_cnt[blockIdx.x];
+    if (kTop) {
+        tile_off = s_top[4]; // (the scan above has synchronised the block)
+    } else {
+        tile_off.c = tile_cnt[blockIdx.x];
 #pragma unroll
-    for (int d = 0; d < D; ++d) tile_off.s[d] = tile_sum[int64_t(blockIdx.x) * D + d];
+        for (int d = 0; d < D; ++d) tile_off.s[d] = tile_sum[int64_t(blockIdx.x) * D + d];
+    }
     run = scan_add(tile_off, run);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -650,8 +677,10 @@ void launch_tree(int64_t n, double theta2, void *ws, const Layout &L, const Tree
     unsigned gn = unsigned((n + 255) / 256);
     tree_splits_kernel<D><<<unsigned((n + kSplitBlock - 1) / kSplitBlock), kSplitBlock, 0, st>>>(codes, n, lm, sb, se);
     scan_reduce_kernel<D, T><<<unsigned(L.scan_tiles), kScanBlock, 0, st>>>(codes, lm, ys, hdr, n, tc, ts);
-    scan_top_kernel<D><<<1, kScanBlock, 0, st>>>(tc, ts, L.scan_tiles, n, base, psum, hdr);
-    scan_down_kernel<D, T><<<unsigned(L.scan_tiles), kScanBlock, 0, st>>>(codes, lm, ys, hdr, n, tc, ts, base, psum);
+    const bool top = L.scan_tiles <= kScanBlock;
+    if (!top) scan_top_kernel<D><<<1, kScanBlock, 0, st>>>(tc, ts, L.scan_tiles, n, base, psum, hdr);
+    auto *down = top ? scan_down_kernel<D, T, true> : scan_down_kernel<D, T, false>;
+    down<<<unsigned(L.scan_tiles), kScanBlock, 0, st>>>(codes, lm, ys, hdr, n, tc, ts, base, psum);
     tree_nodes_kernel<D, T><<<gn, 256, 0, st>>>(codes, n, lm, sb, se, base, psum, ys, hdr, theta2,
                                                 at<char>(ws, L.nodes), dbg);
 }

@@ -66,3 +66,25 @@ def test_fp64_and_layouts(n):
         # the bars of the fp64 parity tests
         assert np.linalg.norm(g.cpu().numpy() - go) <= 1e-9 * np.linalg.norm(go)
         assert abs(Z - Zo) <= 1e-12 * Zo
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2**18, 2**18 + 1])
+def test_cell_sums(n):
+    """Up to 256 tiles of 1024 points the tiles' totals are scanned by every block: the
+    centre of each cell is its points' mean, within fp32 rounding of it and (cells of
+    more than 32 points) of a difference of two fp64 prefix sums of y - centre"""
+    y = _points("random", n, 2)
+    t = bh.debug_tree(torch.from_numpy(y).to(DEV))
+    _, _, perm, params = bh.debug_sort(torch.from_numpy(y).to(DEV))
+    ys = y[perm.cpu().numpy().view(np.uint32)].astype(np.longdouble)
+    b, e = (t[k].cpu().numpy().view(np.uint32).astype(np.int64) for k in ("begin", "end"))
+    assert b[0] == 0 and e[0] == n and b.size == t["nodes"]
+    sums = np.concatenate([np.zeros((1, 2), np.longdouble), np.cumsum(ys, 0)])
+    cnt = (e - b)[:, None]
+    com = ((sums[e] - sums[b]) / cnt).astype(np.float64)
+    smax = np.abs(y.astype(np.float64) - np.array(params[4:6])).sum(0)
+    # (1e-12: the rounding of this reference, prefix sums of 80-bit floats up to 3e6)
+    tol = 7e-8 * np.abs(com) + np.where(cnt > 32, 8 * 2.0 ** -52 * smax / cnt, 0.0) + 1e-12 / cnt
+    summ = t["summary"].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(summ[:, :2] - com) <= tol)
+    assert np.array_equal(summ[:, 2], cnt[:, 0])
