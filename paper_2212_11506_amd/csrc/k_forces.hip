@@ -90,11 +90,14 @@ __device__ inline void keep_loaded(const u32x8 &r) { asm volatile("" ::"s"(r[5])
 // A visit is a chain: the record's scalar load, the compares, the choice of the
 // next record.  With kAhead the next record is loaded as soon as it is chosen,
 // before the accumulation of the one in hand, which takes as long as the
-// compares; two visits a round alternate between two sets of registers, so
-// nothing is moved.  The load past the last record stays inside the array's
-// padding.  (3-D 150k points 718 -> 622 us, fp64 400k 451 -> 424, 2-D fp32 150k 151 ->
-// 139.  With 8 waves a SIMD the 2-D fp32 walk is bound by issue and the simple loop
-// as fast: 1M points 447 us against 455.)
+// compares; two visits a round alternate between two sets of registers, and only
+// the second asks for the end, so nothing is moved (with an exit after either the
+// sums were, at three vector instructions a visit): the record at `end` is one that
+// no lane takes and whose successor lies past it, and the load after that reads at
+// most 32 bytes into the array that follows.  (Loading ahead: 3-D 150k points 718 ->
+// 622 us, fp64 400k 451 -> 424, 2-D fp32 150k 151 -> 139.  One exit a round: whole
+// steps at 70k points 205 -> 195 us.  With 8 waves a SIMD the 2-D fp32 walk is bound
+// by issue, and the simple loop, which picks the next record last, serves there.)
 template <bool kSelf, bool kAhead>
 __device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi, uint32_t si, uint32_t &resume,
                                       float &fx, float &fy, float &z, uint32_t &inter)
@@ -112,24 +115,27 @@ __device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi
         uint64_t take = act & mask_ogt(d2, thr);
         if (kSelf) take &= mask_ne(r[5], si);
         // the first child follows its cell; no lane descends: jump past the subtree
-        cur = take != act ? cur + kNodeBytes : next;
         if (kAhead) {
+            cur = take != act ? cur + kNodeBytes : next;
             after = load_record(nbase, cur);
             __builtin_amdgcn_sched_barrier(0);
         }
         inter += uint32_t(__builtin_popcountll(take));
         take_node(take, d2, dx, dy, cnt, next, z, fx, fy, resume);
-        return cur < end;
+        if (!kAhead) cur = take != act ? cur + kNodeBytes : next;
     };
     if (!kAhead) {
         u32x8 none;
-        while (visit(load_record(nbase, cur), none)) {
-        }
+        do {
+            visit(load_record(nbase, cur), none);
+        } while (cur < end);
         return;
     }
-    u32x8 a = load_record(nbase, cur), b = a;
-    while (visit(a, b) && visit(b, a)) {
-    }
+    u32x8 a = load_record(nbase, cur), b;
+    do {
+        visit(a, b);
+        visit(b, a);
+    } while (cur < end);
     keep_loaded(a);
     keep_loaded(b);
 }
@@ -185,11 +191,12 @@ __device__ inline void repulsive_walk3(const char *nbase, uint32_t end, float3 y
         __builtin_amdgcn_sched_barrier(0);
         inter += uint32_t(__builtin_popcountll(take));
         take_node3(take, d2, dx, dy, dz, cnt, next, z, fx, fy, fz, resume);
-        return cur < end;
     };
-    u32x8 a = load_record(nbase, cur), b = a;
-    while (visit(a, b) && visit(b, a)) {
-    }
+    u32x8 a = load_record(nbase, cur), b;
+    do { // (two visits a round, as in 2-D)
+        visit(a, b);
+        visit(b, a);
+    } while (cur < end);
     keep_loaded(a);
     keep_loaded(b);
 }

@@ -62,3 +62,16 @@ def test_walk_3d(n, theta):
     ws = torch.empty(bh.workspace_size_3d(n, P.nnz), dtype=torch.uint8, device=DEV)
     g, Z = bh.gradient_3d(torch.from_numpy(Y).to(DEV), P, theta, ALPHA, workspace=ws)
     _check(g.cpu().numpy(), Z, bh.get_stats(ws)["interactions"], oracle.gradient3(Y, *p, theta, ALPHA), (1e-3, 1e-5, 1e-3))
+
+
+# one bucket: the walk visits every record, an odd or even number of them, up to the one that ends it
+@pytest.mark.parametrize("n", [480 * 64 + 1, 480 * 64 + 2])
+@pytest.mark.parametrize("d", [2, 3])
+@pytest.mark.parametrize("theta", [0.5, 0.8])
+def test_walk_one_bucket(n, d, theta):
+    Y = torch.full((n, d), 1.5, device=DEV)
+    P = bh.Csr.from_numpy(*_p(n), device=DEV)
+    g, Z = (bh.gradient if d == 2 else bh.gradient_3d)(Y, P, theta, ALPHA)
+    assert not g.any()
+    # each pair weighs exactly 1, and a point's sum of them is below 2^24
+    assert abs(Z - n * (n - 1)) <= 2.0 ** -24 * n * (n - 1)
