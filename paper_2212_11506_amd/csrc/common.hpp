@@ -61,7 +61,7 @@ constexpr int kNodeBytes64 = 40;
 constexpr int kNodeBytes3 = 32;
 template <int D, typename T> constexpr int node_bytes() { return D == 3 ? kNodeBytes3 : (sizeof(T) == 8 ? kNodeBytes64 : kNodeBytes); }
 constexpr uint32_t kNodeCell = 0xFFFFFFFFu;
-// the 2n - 1 records end below 2^32 bytes
+// the 2n + 1 records (40 bytes at most) end below 2^32 bytes
 constexpr int64_t kMaxPoints = (int64_t(1) << 24) - 1;
 constexpr int64_t kYPad = 16384 + 2;                   // padding points after the private copy of Y
 // tiled attractive step: rows in blocks of kTileRows, columns in segments of
@@ -143,8 +143,6 @@ struct Layout {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-inline int64_t spare_for(int64_t n) { return ((n + 1023) / 1024 + 7) / 8 * 8; }
-
 // `fbytes` is the size of a coordinate: 4 (fp32 path) or 8 (fp64 variant,
 // which sizes the copies of Y, the node records and F_rep for fp64); `dim`
 // the embedding's dimension (2, or 3 for the 3-D calls, fp32 only)
@@ -179,19 +177,19 @@ inline Layout make_layout(int64_t n, int64_t nnz, int fbytes = 4, int dim = 2)
     L.psum = take(8 * size_t(dim) * size_t(n + 1));
     L.scan_cnt = take(4 * size_t(L.scan_tiles + 1));
     L.scan_sum = take(8 * size_t(dim) * size_t(L.scan_tiles + 1));
-    // + 8 bytes: the 2-D walk loads 32 bytes at a record's offset
-    L.nodes = take((dim == 3 ? kNodeBytes3 : (fbytes == 8 ? kNodeBytes64 : kNodeBytes)) * size_t(2 * n) + 8);
+    // A tree has at most 2n nodes: n leaves, n - 1 cells that split their points or hold
+    // a run of equal codes, and the root where all points lie in one of its children
+    // (two equal points; fp64 points a few ulps apart).  + the record that ends a
+    // walk; + 8 bytes: the 2-D walk loads 32 bytes at a record's offset
+    L.nodes = take((dim == 3 ? kNodeBytes3 : (fbytes == 8 ? kNodeBytes64 : kNodeBytes)) * size_t(2 * n + 1) + 8);
     L.frep = take(size_t(dim) * size_t(fbytes) * size_t(n));
     L.fattr = take(size_t(dim) * size_t(fbytes) * size_t(n));
     // partial attractive sums, one per (tile, sorted row slot): kTileSlots
     // tiles of kTileRows rows per row block
     L.partial = take(size_t(dim) * size_t(fbytes) * size_t((n + kTileRows - 1) / kTileRows) * kTileRows *
                      size_t(kTileSlots));
-    // (no longer used: the total is what callers sized, and bhtsne_step_noalloc's limit)
-    take(8 * size_t(spare_for(n)));
     const int64_t zb = (n + kZEvalPoints - 1) / kZEvalPoints;
     L.eval_part = take(8 * size_t(zb > kEvalMaxBlocks ? zb : kEvalMaxBlocks));
-    take(8 * size_t(spare_for(n)));
     L.total = off;
     return L;
 }

@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     uint32_t resume = valid ? 0u : 0xffffffffu;
     T fx = 0, fy = 0, fz = 0, z = 0;
     uint32_t total = uniform(hdr->nodes);
-    const uint32_t cap = uint32_t(2 * n - 1);
+    const uint32_t cap = uint32_t(2 * n);
     total = total < cap ? total : cap;
     // Every record's next offset lies past the record (the tree kernel checks
     // it and flags the call otherwise), so each visit advances and the walk

@@ -579,14 +579,12 @@ __global__ __launch_bounds__(256) void tree_nodes_kernel(
         }
     };
     // The record that ends the walks which visit two records a round: no lane takes
-    // it, and what follows it lies past the end.  There are at most 2n - 1 nodes from
-    // three points on (the widest extent puts points into different children of the
-    // root, unless all are one bucket), so it has room.
+    // it, and what follows it lies past the end.  A tree has at most 2n nodes.
     if (x == 0) {
         const int64_t total = base[n];
-        if (total < 2 * n)
+        if (total <= 2 * n)
             store_node(nodes, total, point_t<D, T>{}, 0.0f, T(INFINITY), uint32_t((total + 1) * kBytes), kNodeCell);
-        else if (total > 2 * n)
+        else
             atomicOr(&hdr->flags, kErrRange);
     }
     if (x < n) {

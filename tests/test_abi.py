@@ -38,7 +38,7 @@ def test_workspace_size():
     assert bh.workspace_size(-5, 0) == 0
     assert bh.workspace_size(2, -1) == 0
     assert bh.workspace_size(1 << 26, 0) == 0
-    # skip indices of the 2n - 1 node records take 25 bits: n < 2^24
+    # a point takes 24 bits in the packed keys and row entries: n < 2^24
     assert bh.workspace_size(1 << 24, 0) == 0
     assert bh.workspace_size((1 << 24) - 1, 0) > 0
     a = bh.workspace_size(1000, 10)

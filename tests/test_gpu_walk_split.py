@@ -75,3 +75,36 @@ def test_walk_one_bucket(n, d, theta):
     assert not g.any()
     # each pair weighs exactly 1, and a point's sum of them is below 2^24
     assert abs(Z - n * (n - 1)) <= 2.0 ** -24 * n * (n - 1)
+
+
+# Trees of 2n nodes, the most there are: the root has one child, which holds every
+# point.  In fp32 only two equal points make one; in fp64 also a box a few ulps wide,
+# whose centre rounds to its lower end.
+@pytest.mark.parametrize("theta", [0.0, 0.5, 0.8])
+@pytest.mark.parametrize("form", ["f32", "layout", "f64", "3d"])
+def test_two_equal_points(form, theta):
+    Y = torch.full((2, 3 if form == "3d" else 2), 1.5, dtype=torch.float64 if form == "f64" else torch.float32, device=DEV)
+    size, grad = {"f64": (bh.workspace_size_f64, bh.gradient_f64), "3d": (bh.workspace_size_3d, bh.gradient_3d)}.get(
+        form, (bh.workspace_size, bh.gradient))
+    P = (bh.CsrF64 if form == "f64" else bh.Csr).from_numpy(*_p(2), device=DEV)
+    ws = torch.empty(size(2, P.nnz), dtype=torch.uint8, device=DEV)
+    if form == "layout":
+        P = bh.Layout(P, Y, workspace=ws)
+    g, Z = grad(Y, P, theta, ALPHA, workspace=ws)
+    stats = bh.get_stats(ws)
+    assert stats["nodes"] == 4 and stats["interactions"] == 2
+    assert Z == 2.0 and not g.any()
+
+
+@pytest.mark.parametrize("ulps", [[0, 0, 1], [0, 0, 1, 1], [1, 0, 0, 1]])
+def test_full_tree_f64(ulps):
+    n = len(ulps)
+    Y = np.stack([1.0 + np.array(ulps) * 2.0 ** -52, np.full(n, 2.0)], 1)
+    p = _p(n)
+    P = bh.CsrF64.from_numpy(*p, device=DEV)
+    ws = torch.empty(bh.workspace_size_f64(n, P.nnz), dtype=torch.uint8, device=DEV)
+    g, Z = bh.gradient_f64(torch.from_numpy(Y).to(DEV), P, 0.5, ALPHA, workspace=ws)
+    assert bh.get_stats(ws)["nodes"] == 2 * n
+    assert Z == n * (n - 1)  # every weight rounds to 1
+    go = oracle.gradient(Y, *p, 0.5, ALPHA)[0]
+    assert np.linalg.norm(g.cpu().numpy() - go) <= 1e-9 * np.linalg.norm(go)
