@@ -424,8 +424,9 @@ __device__ inline int walk_list(const char *nbase, uint32_t &cur, uint32_t end, 
 
 // Adds up `len` listed entries in their order.  An entry is read by all lanes at
 // once; a lane outside its mask counts it 0 times, which leaves its sums as they
-// are.
-template <int D>
+// are, unless the entry is infinitely far from it in fp32 (0 times infinity): where
+// the box is that wide (kWide) such a lane also takes the distance for 0.
+template <int D, bool kWide>
 __device__ inline void add_list(const Lists &l, int first, int len, const point_t<D, float> &yi, float &fx, float &fy,
                                 float &fz, float &z)
 {
@@ -433,15 +434,19 @@ __device__ inline void add_list(const Lists &l, int first, int len, const point_
     const uint32_t *mask = (lane_id() < 32 ? l.lo : l.hi) + first;
     const uint32_t bit = lane_id() & 31;
     auto add = [&](const float4 &e, uint32_t m) {
-        const float cnt = (m >> bit) & 1u ? (D == 3 ? e.w : e.z) : 0.0f;
-        const float dx = coord(yi, 0) - e.x, dy = coord(yi, 1) - e.y;
-        float dz = 0.0f, d2;
-        if constexpr (D == 3) {
-            dz = coord(yi, 2) - e.z;
-            d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        } else {
-            d2 = fmaf(dx, dx, dy * dy);
+        const bool in = (m >> bit) & 1u;
+        const float cnt = in ? (D == 3 ? e.w : e.z) : 0.0f;
+        float dx = coord(yi, 0) - e.x, dy = coord(yi, 1) - e.y, dz = 0.0f, d2;
+        if constexpr (D == 3) dz = coord(yi, 2) - e.z;
+        if constexpr (kWide) {
+            dx = in ? dx : 0.0f;
+            dy = in ? dy : 0.0f;
+            dz = in ? dz : 0.0f;
         }
+        if constexpr (D == 3)
+            d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        else
+            d2 = fmaf(dx, dx, dy * dy);
         const float w = fast_rcp(1.0f + d2);
         float t = cnt * w;
         z = fmaf(cnt, w, z);
@@ -472,8 +477,8 @@ __device__ inline void add_list(const Lists &l, int first, int len, const point_
 // round, so the rounds end.
 template <int D, bool kSelf>
 __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end, const point_t<D, float> &yi,
-                                   uint32_t si, uint32_t me, int log_waves, uint32_t &resume, float &fx, float &fy,
-                                   float &fz, float &z, uint32_t &inter, const Lists &l)
+                                   uint32_t si, uint32_t me, int log_waves, bool wide, uint32_t &resume, float &fx,
+                                   float &fy, float &fz, float &z, uint32_t &inter, const Lists &l)
 {
     const int w = int(uniform(threadIdx.x / kWave)), lead = w - int(me), parts = 1 << log_waves;
     int len = 0, part = 0; // part: the first one that is not added up yet
@@ -487,7 +492,11 @@ __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end
         __syncthreads();
         if (me == 0) {
             while (part < parts) {
-                add_list<D>(l, (lead + part) * kListRoom, int(uniform(uint32_t(l.len[lead + part]))), yi, fx, fy, fz, z);
+                const int first = (lead + part) * kListRoom, listed = int(uniform(uint32_t(l.len[lead + part])));
+                if (wide)
+                    add_list<D, true>(l, first, listed, yi, fx, fy, fz, z);
+                else
+                    add_list<D, false>(l, first, listed, yi, fx, fy, fz, z);
                 if (!uniform(uint32_t(l.done[lead + part]))) break; // its list is empty now
                 ++part;
             }
@@ -563,10 +572,12 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     if constexpr (kSplit && sizeof(T) == 4) {
         extern __shared__ float4 s_lists[];
         const Lists lists(reinterpret_cast<char *>(s_lists), waves);
+        // two points of the box may differ by more than the largest float
+        const bool wide = !(hdr->rspan < 1e38);
         if (self_test)
-            walk_shared<D, true>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+            walk_shared<D, true>(nodes, cur, end, yi, si, me, log_waves, wide, resume, fx, fy, fz, z, inter, lists);
         else
-            walk_shared<D, false>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+            walk_shared<D, false>(nodes, cur, end, yi, si, me, log_waves, wide, resume, fx, fy, fz, z, inter, lists);
     } else if constexpr (D == 3) {
         if (self_test)
             repulsive_walk3<true>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);

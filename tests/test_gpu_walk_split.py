@@ -108,3 +108,15 @@ def test_full_tree_f64(ulps):
     assert Z == n * (n - 1)  # every weight rounds to 1
     go = oracle.gradient(Y, *p, 0.5, ALPHA)[0]
     assert np.linalg.norm(g.cpu().numpy() - go) <= 1e-9 * np.linalg.norm(go)
+
+
+# At an angle this wide the outer points take the root, while the two at its centre
+# take every point one by one: for an outer point one of those lies at a distance
+# beyond the largest float, and must leave its sums alone.
+@pytest.mark.parametrize("d", [2, 3])
+def test_box_wider_than_the_largest_float(d):
+    Y = torch.zeros((4, d), device=DEV)  # (four, each child of the root holds one place: its centre is 0 exactly)
+    Y[0, 0], Y[0, 1], Y[1, 0], Y[1, 1] = -2e38, 1e38, 2e38, -1e38
+    P = bh.Csr.from_numpy(np.zeros(5, np.int64), np.zeros(0, np.int32), np.zeros(0, np.float32), device=DEV)
+    g, Z = (bh.gradient if d == 2 else bh.gradient_3d)(Y, P, 1e30, 1.0)
+    assert Z == 2.0 and not g.any()  # two equal points; everything else weighs 0
