@@ -510,19 +510,26 @@ __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end
 }
 
 // D = 2, T = float: the path (24-byte records); T = double: the fp64
-// variant; D = 3: 3-D embeddings (32-byte records).  kSplit: 2^log_waves waves
-// of a block share each group of 64 points, each walking a part of the records.
-template <int D, typename T, bool kSplit>
+// variant; D = 3: 3-D embeddings (32-byte records).  kForm: one wave walks for a
+// group of 64 points, by the simple loop (2-D fp32, blocks of kRepBlock) or loading
+// ahead, or 2^log_waves waves of a block share the group, each walking a part of
+// the records.  Each is a kernel of its own: with the simple and the load-ahead
+// loop in one kernel, which chose at run time, the simple one's walk took 0.5 to 0.8%
+// longer (700k points 382.2 us, now 378.8; 1M at theta 0.2 1397.7, now 1389.0).
+enum WalkForm { kSimple, kAhead, kShared };
+
+template <int D, typename T, int kForm>
 __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     const char *__restrict__ nodes, const point_t<D, T> *__restrict__ ys, const uint32_t *__restrict__ perm,
     const uint32_t *__restrict__ base, Header *__restrict__ hdr, int64_t n, int self_test, int log_waves,
-    int ahead, point_t<D, T> *__restrict__ frep, double *__restrict__ zpart, unsigned long long *__restrict__ ipart)
+    point_t<D, T> *__restrict__ frep, double *__restrict__ zpart, unsigned long long *__restrict__ ipart)
 {
+    constexpr bool kSplit = kForm == kShared;
     using V = point_t<D, T>;
     const uint32_t nb = gridDim.x;
     const uint32_t lb = xcd_contiguous(blockIdx.x, nb);
     const int w = threadIdx.x / kWave;
-    const uint32_t threads = blockDim.x; // at most kRepBlock
+    const uint32_t threads = kForm == kSimple ? kRepBlock : blockDim.x; // at most kRepBlock
     const int waves = int(threads) / kWave;
     uint32_t me = 0; // this wave's number among those of its group
     int64_t s64 = int64_t(lb) * threads + threadIdx.x;
@@ -543,7 +550,7 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     // ends after at most `total` visits.  A flagged tree is not walked.
     if (uniform(hdr->flags) & (kErrLookback | kErrRange)) total = 0;
     uint32_t cur = 0, end = total * uint32_t(node_bytes<D, T>());
-    uint32_t touched = 0;
+    [[maybe_unused]] uint32_t touched = 0;
     if constexpr (kSplit) {
         // The records were written through other XCDs' caches.  Where they fit
         // this XCD's (4 MB) its blocks fetch them together, one load a line,
@@ -588,18 +595,13 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
             repulsive_walk64<true>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
         else
             repulsive_walk64<false>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
-    } else if (ahead) {
-        if (self_test)
-            repulsive_walk<true, true>(nodes, end, yi, si, resume, fx, fy, z, inter);
-        else
-            repulsive_walk<false, true>(nodes, end, yi, si, resume, fx, fy, z, inter);
     } else {
         if (self_test)
-            repulsive_walk<true, false>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<true, kForm == kAhead>(nodes, end, yi, si, resume, fx, fy, z, inter);
         else
-            repulsive_walk<false, false>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<false, kForm == kAhead>(nodes, end, yi, si, resume, fx, fy, z, inter);
     }
-    asm volatile("" ::"v"(touched)); // the loads above are wanted, not their values
+    if constexpr (kSplit) asm volatile("" ::"v"(touched)); // the loads above are wanted, not their values
     bool lead = true; // this wave finishes its group's points
     if constexpr (kSplit) {
         lead = me == 0;
@@ -783,8 +785,8 @@ __global__ __launch_bounds__(256) void attract_kernel(
 }
 
 // ------------------------------------------------------------------ launchers
-// How a walk is launched: log2 of the waves that share a group of 64 points, the
-// threads of a block, and whether one wave's 2-D fp32 walk loads ahead.
+// How a walk is launched: its form, log2 of the waves that share a group of 64
+// points, and the threads of a block.
 //
 // A walk is a chain of dependent record loads (some 300 ns a record alone on a
 // SIMD, 500 to 900 records a group), so few groups leave the chip waiting, and
@@ -795,31 +797,33 @@ __global__ __launch_bounds__(256) void attract_kernel(
 // sharing pays only where the walks themselves are many times longer than that.
 // Blocks of consecutive points share records through the scalar cache, 1024
 // points best where every CU has several blocks; smaller ones reach more CUs and
-// end sooner.  Walk in us, gfx950, theta 0.5, the start's in brackets:
+// end sooner.  Walk in us, gfx950, theta 0.5, in brackets one wave a group by the
+// simple loop in blocks of 1024 threads:
 //   fp32  8 waves a group: 2k points (94) 52, 10k (115) 65, 30k (112) 82;
 //         1 wave, ahead, 256 threads: 2k 81, 10k 98, 30k 89, 70k (165) 134, 150k (151)
 //         141, 300k (226) 200, 500k 256; 1024 threads, simple: 500k 235, 1M 447
 //   fp64  5k (203) 41 with 16 waves, 50k (237) 79 with 4, 200k (281) 198 with 2, 400k
 //         (451) 374 with 2; 600k 503 with 1 and 512 threads, 562 with 1024
 //   3-D   5k (328) 181 with 16 waves, 225 with 1; 20k 203 against 208; 1 wave, 256
-//         threads: 50k (397) 299, 150k (718) 539, 800k (1412) 1425 early, 1.3M (2246) 2214
+//         threads: 50k (397) 299, 150k (718) 539, 300k (930) 664, 800k (1717) 1380 early
+//         and (1371) 1119 late in a run, 1.3M (2503) 2049
 struct WalkLaunch {
+    WalkForm form;
     int log_waves, threads;
-    bool ahead;
 };
 
 template <int D, typename T> static WalkLaunch walk_launch(int64_t n)
 {
     const int64_t groups = (n + kWave - 1) / kWave;
-    if (D == 3) return groups <= 128 ? WalkLaunch{4, 1024, true} : WalkLaunch{0, 256, true};
+    if (D == 3) return groups <= 128 ? WalkLaunch{kShared, 4, 1024} : WalkLaunch{kAhead, 0, 256};
     if (sizeof(T) == 8) {
         for (int lw = 4; lw > 1; --lw)
-            if (groups << lw <= 4096) return {lw, std::max(512, kWave << lw), true};
-        return {groups <= 8192 ? 1 : 0, 512, true};
+            if (groups << lw <= 4096) return {kShared, lw, std::max(512, kWave << lw)};
+        return groups <= 8192 ? WalkLaunch{kShared, 1, 512} : WalkLaunch{kAhead, 0, 512};
     }
-    if (groups <= 480) return {3, 512, true};
-    if (groups <= 6400) return {0, 256, true};
-    return {0, kRepBlock, false};
+    if (groups <= 480) return {kShared, 3, 512};
+    if (groups <= 6400) return {kAhead, 0, 256};
+    return {kSimple, 0, kRepBlock};
 }
 
 template <int D, typename T>
@@ -832,11 +836,13 @@ void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipS
     // the blocks' partials go to the sort's second key array, free by now: 16
     // bytes for at least 64 points, in 8 bytes a point (and 256 at the least)
     double *zpart = at<double>(ws, L.codes1);
-    auto *kernel = c.log_waves ? repulsive_kernel<D, T, true> : repulsive_kernel<D, T, false>;
-    const size_t lds = c.log_waves && sizeof(T) == 4 ? Lists::bytes(c.threads / kWave) : 0;
+    auto *kernel = c.form == kShared ? repulsive_kernel<D, T, kShared> : repulsive_kernel<D, T, kAhead>;
+    if constexpr (D == 2 && sizeof(T) == 4)
+        if (c.form == kSimple) kernel = repulsive_kernel<D, T, kSimple>;
+    const size_t lds = c.form == kShared && sizeof(T) == 4 ? Lists::bytes(c.threads / kWave) : 0;
     kernel<<<unsigned(blocks), unsigned(c.threads), lds, st>>>(
         at<char>(ws, L.nodes), at<V>(ws, L.ys), at<uint32_t>(ws, L.idx0), at<uint32_t>(ws, L.base),
-        at<Header>(ws, L.header), n, self_test ? 1 : 0, c.log_waves, c.ahead ? 1 : 0, at<V>(ws, L.frep), zpart,
+        at<Header>(ws, L.header), n, self_test ? 1 : 0, c.log_waves, at<V>(ws, L.frep), zpart,
         reinterpret_cast<unsigned long long *>(zpart + blocks));
 }
 template void launch_repulsive<2, float>(int64_t, bool, void *, const Layout &, hipStream_t);
