@@ -340,6 +340,10 @@ __device__ inline uint32_t part_bound(uint32_t q, uint32_t parts, uint32_t mid, 
 // later.)  Listing leaves out the reciprocal and the sums, 10 vector instructions
 // a visit instead of 14, and adding up has no chain but the sums.
 constexpr int kListRoom = 256; // entries of a wave's list
+// Half the widest box that waves share.  In a wider one an entry may be infinitely
+// far in fp32 from a lane that does not take it, and counting it 0 times would make
+// the lane's sums NaN; the group's first wave walks alone there.
+constexpr double kWidest = 1e38;
 
 struct Lists { // in LDS, `waves` lists of kListRoom entries
     float4 *c;
@@ -424,9 +428,8 @@ __device__ inline int walk_list(const char *nbase, uint32_t &cur, uint32_t end, 
 
 // Adds up `len` listed entries in their order.  An entry is read by all lanes at
 // once; a lane outside its mask counts it 0 times, which leaves its sums as they
-// are, unless the entry is infinitely far from it in fp32 (0 times infinity): where
-// the box is that wide (kWide) such a lane also takes the distance for 0.
-template <int D, bool kWide>
+// are.  (The distance must be finite in fp32: see kWidest.)
+template <int D>
 __device__ inline void add_list(const Lists &l, int first, int len, const point_t<D, float> &yi, float &fx, float &fy,
                                 float &fz, float &z)
 {
@@ -434,19 +437,15 @@ __device__ inline void add_list(const Lists &l, int first, int len, const point_
     const uint32_t *mask = (lane_id() < 32 ? l.lo : l.hi) + first;
     const uint32_t bit = lane_id() & 31;
     auto add = [&](const float4 &e, uint32_t m) {
-        const bool in = (m >> bit) & 1u;
-        const float cnt = in ? (D == 3 ? e.w : e.z) : 0.0f;
-        float dx = coord(yi, 0) - e.x, dy = coord(yi, 1) - e.y, dz = 0.0f, d2;
-        if constexpr (D == 3) dz = coord(yi, 2) - e.z;
-        if constexpr (kWide) {
-            dx = in ? dx : 0.0f;
-            dy = in ? dy : 0.0f;
-            dz = in ? dz : 0.0f;
-        }
-        if constexpr (D == 3)
+        const float cnt = (m >> bit) & 1u ? (D == 3 ? e.w : e.z) : 0.0f;
+        const float dx = coord(yi, 0) - e.x, dy = coord(yi, 1) - e.y;
+        float dz = 0.0f, d2;
+        if constexpr (D == 3) {
+            dz = coord(yi, 2) - e.z;
             d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        else
+        } else {
             d2 = fmaf(dx, dx, dy * dy);
+        }
         const float w = fast_rcp(1.0f + d2);
         float t = cnt * w;
         z = fmaf(cnt, w, z);
@@ -477,8 +476,8 @@ __device__ inline void add_list(const Lists &l, int first, int len, const point_
 // round, so the rounds end.
 template <int D, bool kSelf>
 __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end, const point_t<D, float> &yi,
-                                   uint32_t si, uint32_t me, int log_waves, bool wide, uint32_t &resume, float &fx,
-                                   float &fy, float &fz, float &z, uint32_t &inter, const Lists &l)
+                                   uint32_t si, uint32_t me, int log_waves, uint32_t &resume, float &fx, float &fy,
+                                   float &fz, float &z, uint32_t &inter, const Lists &l)
 {
     const int w = int(uniform(threadIdx.x / kWave)), lead = w - int(me), parts = 1 << log_waves;
     int len = 0, part = 0; // part: the first one that is not added up yet
@@ -492,11 +491,7 @@ __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end
         __syncthreads();
         if (me == 0) {
             while (part < parts) {
-                const int first = (lead + part) * kListRoom, listed = int(uniform(uint32_t(l.len[lead + part])));
-                if (wide)
-                    add_list<D, true>(l, first, listed, yi, fx, fy, fz, z);
-                else
-                    add_list<D, false>(l, first, listed, yi, fx, fy, fz, z);
+                add_list<D>(l, (lead + part) * kListRoom, int(uniform(uint32_t(l.len[lead + part]))), yi, fx, fy, fz, z);
                 if (!uniform(uint32_t(l.done[lead + part]))) break; // its list is empty now
                 ++part;
             }
@@ -507,6 +502,17 @@ __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end
         if (int(me) == part) len = 0;
         if (__syncthreads_and(part == parts)) return;
     }
+}
+
+// One wave's walk over all records, which end at `all`.
+template <int D, bool kSelf>
+__device__ inline void walk_alone(const char *nbase, uint32_t all, const point_t<D, float> &yi, uint32_t si,
+                                  uint32_t &resume, float &fx, float &fy, float &fz, float &z, uint32_t &inter)
+{
+    if constexpr (D == 3)
+        repulsive_walk3<kSelf>(nbase, all, yi, si, resume, fx, fy, fz, z, inter);
+    else
+        repulsive_walk<kSelf, false>(nbase, all, yi, si, resume, fx, fy, z, inter);
 }
 
 // D = 2, T = float: the path (24-byte records); T = double: the fp64
@@ -549,7 +555,8 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     // it and flags the call otherwise), so each visit advances and the walk
     // ends after at most `total` visits.  A flagged tree is not walked.
     if (uniform(hdr->flags) & (kErrLookback | kErrRange)) total = 0;
-    uint32_t cur = 0, end = total * uint32_t(node_bytes<D, T>());
+    const uint32_t all = total * uint32_t(node_bytes<D, T>());
+    uint32_t cur = 0, end = all;
     [[maybe_unused]] uint32_t touched = 0;
     if constexpr (kSplit) {
         // The records were written through other XCDs' caches.  Where they fit
@@ -578,13 +585,20 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     uint32_t inter = 0; // this wave's interactions (a launch has fewer than 2^32 per wave)
     if constexpr (kSplit && sizeof(T) == 4) {
         extern __shared__ float4 s_lists[];
+        const bool wide = uniform(hdr->rspan < kWidest ? 0u : 1u) != 0;
         const Lists lists(reinterpret_cast<char *>(s_lists), waves);
-        // two points of the box may differ by more than the largest float
-        const bool wide = !(hdr->rspan < 1e38);
-        if (self_test)
-            walk_shared<D, true>(nodes, cur, end, yi, si, me, log_waves, wide, resume, fx, fy, fz, z, inter, lists);
-        else
-            walk_shared<D, false>(nodes, cur, end, yi, si, me, log_waves, wide, resume, fx, fy, fz, z, inter, lists);
+        if (wide) {
+            if (me == 0) {
+                if (self_test)
+                    walk_alone<D, true>(nodes, all, yi, si, resume, fx, fy, fz, z, inter);
+                else
+                    walk_alone<D, false>(nodes, all, yi, si, resume, fx, fy, fz, z, inter);
+            }
+        } else if (self_test) {
+            walk_shared<D, true>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+        } else {
+            walk_shared<D, false>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+        }
     } else if constexpr (D == 3) {
         if (self_test)
             repulsive_walk3<true>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
