@@ -349,7 +349,7 @@ struct Lists { // in LDS, `waves` lists of kListRoom entries
     float4 *c;
     uint32_t *lo, *hi;
     int *len, *done, *part;
-    static size_t bytes(int waves) { return size_t(waves) * (kListRoom * 24 + 12); }
+    static size_t bytes(int waves) { return size_t(waves) * (kListRoom * 24 + 8) + 4; }
     __device__ Lists(char *m, int waves)
     {
         c = reinterpret_cast<float4 *>(m);
@@ -470,37 +470,36 @@ __device__ inline void add_list(const Lists &l, int first, int len, const point_
     for (; k < len; ++k) add(c[k], mask[k]);
 }
 
-// The walk of a group's waves.  Where a list fills up before its part ends, the
-// waves meet, the first adds up what comes next in order, and the part whose
-// list that emptied walks on: at least one part ends or empties its list each
-// round, so the rounds end.
+// The walk of a block's waves, which share one group of points.  Where a list fills
+// up before its part ends, the waves meet, the first adds up what comes next in
+// order, and the part whose list that emptied walks on: at least one part ends or
+// empties its list each round, so the rounds end.
 template <int D, bool kSelf>
 __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end, const point_t<D, float> &yi,
-                                   uint32_t si, uint32_t me, int log_waves, uint32_t &resume, float &fx, float &fy,
-                                   float &fz, float &z, uint32_t &inter, const Lists &l)
+                                   uint32_t si, int me, int parts, uint32_t &resume, float &fx, float &fy, float &fz,
+                                   float &z, uint32_t &inter, const Lists &l)
 {
-    const int w = int(uniform(threadIdx.x / kWave)), lead = w - int(me), parts = 1 << log_waves;
     int len = 0, part = 0; // part: the first one that is not added up yet
     for (;;) {
-        if (int(me) >= part)
-            len = walk_list<D, kSelf>(nbase, cur, end, yi, si, resume, inter, l, w * kListRoom, len);
+        if (me >= part) len = walk_list<D, kSelf>(nbase, cur, end, yi, si, resume, inter, l, me * kListRoom, len);
         if (lane_id() == 0) {
-            l.len[w] = len;
-            l.done[w] = cur >= end;
+            l.len[me] = len;
+            l.done[me] = cur >= end;
         }
         __syncthreads();
         if (me == 0) {
             while (part < parts) {
-                add_list<D>(l, (lead + part) * kListRoom, int(uniform(uint32_t(l.len[lead + part]))), yi, fx, fy, fz, z);
-                if (!uniform(uint32_t(l.done[lead + part]))) break; // its list is empty now
+                add_list<D>(l, part * kListRoom, int(uniform(uint32_t(l.len[part]))), yi, fx, fy, fz, z);
+                if (!uniform(uint32_t(l.done[part]))) break; // its list is empty now
                 ++part;
             }
-            if (lane_id() == 0) l.part[w] = part;
+            if (lane_id() == 0) *l.part = part;
         }
         __syncthreads();
-        part = int(uniform(uint32_t(l.part[lead])));
-        if (int(me) == part) len = 0;
-        if (__syncthreads_and(part == parts)) return;
+        // (read by all before any wave passes the next round's first barrier)
+        part = int(uniform(uint32_t(*l.part)));
+        if (part == parts) return;
+        if (me == part) len = 0;
     }
 }
 
@@ -519,7 +518,7 @@ __device__ inline void walk_alone(const char *nbase, uint32_t all, const point_t
 // variant; D = 3: 3-D embeddings (32-byte records).  kForm: one wave walks for a
 // group of 64 points, by the simple loop (2-D fp32, blocks of kRepBlock) or loading
 // ahead, or 2^log_waves waves of a block share the group, each walking a part of
-// the records.  Each is a kernel of its own: with the simple and the load-ahead
+// the records (in fp32 all waves of the block).  Each is a kernel of its own: with the simple and the load-ahead
 // loop in one kernel, which chose at run time, the simple one's walk took 0.5 to 0.8%
 // longer (700k points 382.2 us, now 378.8; 1M at theta 0.2 1397.7, now 1389.0).
 enum WalkForm { kSimple, kAhead, kShared };
@@ -586,7 +585,7 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     if constexpr (kSplit && sizeof(T) == 4) {
         extern __shared__ float4 s_lists[];
         const bool wide = uniform(hdr->rspan < kWidest ? 0u : 1u) != 0;
-        const Lists lists(reinterpret_cast<char *>(s_lists), waves);
+        const Lists lists(reinterpret_cast<char *>(s_lists), waves); // one group a block: me is the wave's number
         if (wide) {
             if (me == 0) {
                 if (self_test)
@@ -595,9 +594,9 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
                     walk_alone<D, false>(nodes, all, yi, si, resume, fx, fy, fz, z, inter);
             }
         } else if (self_test) {
-            walk_shared<D, true>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+            walk_shared<D, true>(nodes, cur, end, yi, si, int(me), waves, resume, fx, fy, fz, z, inter, lists);
         } else {
-            walk_shared<D, false>(nodes, cur, end, yi, si, me, log_waves, resume, fx, fy, fz, z, inter, lists);
+            walk_shared<D, false>(nodes, cur, end, yi, si, int(me), waves, resume, fx, fy, fz, z, inter, lists);
         }
     } else if constexpr (D == 3) {
         if (self_test)
@@ -826,6 +825,7 @@ struct WalkLaunch {
     int log_waves, threads;
 };
 
+// (fp32: kWave << log_waves threads a block that shares, one group)
 template <int D, typename T> static WalkLaunch walk_launch(int64_t n)
 {
     const int64_t groups = (n + kWave - 1) / kWave;
