@@ -392,17 +392,17 @@ __device__ inline int walk_list(const char *nbase, uint32_t &cur, uint32_t end, 
         // the lanes that take it park, and lane `fill` keeps the entry (a record that no
         // lane takes is overwritten by the next)
         uint64_t saved;
-        asm volatile("s_mov_b32 m0, %[fill]\n\t"
-                     "s_and_saveexec_b64 %[sv], %[take]\n\t"
+        asm volatile("s_and_saveexec_b64 %[sv], %[take]\n\t"
                      "v_mov_b32 %[res], %[next]\n\t"
-                     "s_mov_b64 exec, %[sv]\n\t"
-                     "v_writelane_b32 %[rec], %[at], m0\n\t"
-                     "v_writelane_b32 %[lo], %[tlo], m0\n\t"
-                     "v_writelane_b32 %[hi], %[thi], m0"
+                     "s_lshl_b64 exec, 1, %[fill]\n\t"
+                     "v_mov_b32 %[rec], %[at]\n\t"
+                     "v_mov_b32 %[lo], %[tlo]\n\t"
+                     "v_mov_b32 %[hi], %[thi]\n\t"
+                     "s_mov_b64 exec, %[sv]"
                      : [res] "+v"(resume), [sv] "=&s"(saved), [rec] "+v"(rec), [lo] "+v"(lo), [hi] "+v"(hi)
                      : [take] "s"(take), [next] "s"(next), [fill] "s"(fill), [at] "s"(at), [tlo] "s"(uint32_t(take)),
                        [thi] "s"(uint32_t(take >> 32))
-                     : "scc", "m0");
+                     : "scc");
         fill += take != 0 ? 1 : 0;
         return cur < end && fill < kWave;
     };
