@@ -480,6 +480,15 @@ int bhtsne_debug_tree_3d(const float *Y, int64_t n, float theta, int64_t *n_node
                          uint32_t *begin, uint32_t *end, float *summary, float *threshold, uint32_t *meta,
                          void *workspace, size_t workspace_bytes, hipStream_t stream);
 
+/* Test export: F_rep (n x dim float32, caller's order), Z and the interaction
+ * count of a 2-D or 3-D fp32 embedding through one form of the repulsive walk.
+ * Every form adds a point's terms up in the same order, so F_rep agrees bit for
+ * bit.  form: -1 the one that n points take, 0 one wave a group of 64 points
+ * (2-D only), 1 one wave a group, the next record loaded ahead.  workspace:
+ * bhtsne_workspace_size(n, 0), or bhtsne_workspace_size_3d(n, 0) for dim 3. */
+int bhtsne_debug_walk(const float *Y, int64_t n, int dim, float theta, int form, float *frep, double *Z,
+                      uint64_t *interactions, void *workspace, size_t workspace_bytes, hipStream_t stream);
+
 #ifdef __cplusplus
 }
 #endif

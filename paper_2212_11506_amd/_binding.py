@@ -115,6 +115,8 @@ def load_library():
         "bhtsne_debug_sort_3d": (C.c_int, [vp, i64, vp, vp, vp, f64p, vp, C.c_size_t, vp]),
         "bhtsne_debug_tree_3d": (C.c_int, [vp, i64, f32, C.POINTER(C.c_int64), vp, vp, vp, vp, vp, vp, vp, vp,
                                            C.c_size_t, vp]),
+        "bhtsne_debug_walk": (C.c_int, [vp, i64, C.c_int, f32, C.c_int, vp, f64p, C.POINTER(C.c_uint64), vp,
+                                        C.c_size_t, vp]),
         "bhtsne_debug_sort": (C.c_int, [vp, i64, vp, vp, vp, f64p, vp, C.c_size_t, vp]),
         "bhtsne_debug_tree": (C.c_int, [vp, i64, f32, C.POINTER(C.c_int64), vp, vp, vp, vp, vp, vp, vp,
                                         C.c_size_t, vp]),
@@ -638,3 +640,17 @@ def debug_tree_3d(Y: torch.Tensor, theta: float = 0.5, workspace: Optional[torch
     k = nn.value
     return {"nodes": k, "level": level[:k], "kind": kind[:k], "begin": begin[:k], "end": end[:k],
             "summary": summ[:k], "threshold": thr[:k], "meta": meta[:k]}
+
+
+def debug_walk(Y: torch.Tensor, theta: float = 0.5, form: int = -1):
+    """(F_rep, Z, interactions) of a 2-D or 3-D fp32 embedding through one form of the repulsive walk: -1 the
+    one its size takes, 0 one wave a group of 64 points (2-D), 1 one wave a group, loading ahead."""
+    lib = load_library()
+    n, dim = Y.shape
+    ws = _workspace_3d(n, 0, None) if dim == 3 else _workspace(n, 0, None)[0]
+    frep = torch.empty_like(Y)
+    Z, inter = C.c_double(0.0), C.c_uint64(0)
+    rc = lib.bhtsne_debug_walk(_ptr(Y, torch.float32, "Y"), n, dim, float(theta), int(form), _ptr(frep), C.byref(Z),
+                               C.byref(inter), _ptr(ws), ws.numel(), _stream())
+    _check(rc, "bhtsne_debug_walk")
+    return frep, Z.value, inter.value

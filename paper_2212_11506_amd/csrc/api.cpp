@@ -1254,4 +1254,34 @@ int bhtsne_debug_tree(const float *Y, int64_t n, float theta, int64_t *n_nodes, 
     return flags_status(h.flags);
 }
 
+int bhtsne_debug_walk(const float *Y, int64_t n, int dim, float theta, int form, float *frep, double *Z,
+                      uint64_t *interactions, void *workspace, size_t workspace_bytes, hipStream_t stream)
+{
+    if (!Y || !frep || !Z || !interactions || n < 2 || n > kMaxPoints) return BHTSNE_EINVAL;
+    if (!finite_f(theta) || theta < 0.0f) return BHTSNE_EINVAL;
+    if ((dim != 2 && dim != 3) || form < -1 || form > 1 || (dim == 3 && form == 0)) return BHTSNE_EINVAL;
+    int rc = dim == 3 ? check_ws_3d(n, 0, workspace, workspace_bytes) : check_ws(n, 0, workspace, workspace_bytes);
+    if (rc != BHTSNE_OK) return rc;
+    const Layout L = make_layout(n, 0, 4, dim);
+    if (dim == 3) {
+        launch_bbox_morton3(Y, n, nullptr, workspace, L, stream);
+        launch_sort_points(n, reinterpret_cast<const float3 *>(Y), workspace, L, stream);
+        launch_tree<3, float>(n, double(theta) * double(theta), workspace, L, TreeDebug{}, stream);
+        launch_repulsive<3, float>(n, repulsive_self_test3(theta), workspace, L, stream, form);
+    } else {
+        build_tree(Y, n, theta, nullptr, workspace, L, TreeDebug{}, stream);
+        launch_repulsive<2, float>(n, repulsive_self_test(theta), workspace, L, stream, form);
+    }
+    if (hipMemcpyAsync(frep, at<void>(workspace, L.frep), 4 * size_t(dim) * size_t(n), hipMemcpyDeviceToDevice,
+                       stream) != hipSuccess)
+        return BHTSNE_EDEVICE;
+    if (hipGetLastError() != hipSuccess) return BHTSNE_EDEVICE;
+    Header h;
+    rc = read_header(workspace, &h, stream);
+    if (rc != BHTSNE_OK) return rc;
+    *Z = h.Z;
+    *interactions = h.interactions;
+    return flags_status(h.flags);
+}
+
 } // extern "C"

@@ -841,10 +841,11 @@ template <int D, typename T> static WalkLaunch walk_launch(int64_t n)
 }
 
 template <int D, typename T>
-void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st)
+void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st, int form)
 {
     using V = point_t<D, T>;
-    const WalkLaunch c = walk_launch<D, T>(n);
+    WalkLaunch c = walk_launch<D, T>(n);
+    if (form >= 0) c = form == kSimple ? WalkLaunch{kSimple, 0, kRepBlock} : WalkLaunch{kAhead, 0, 256};
     const int64_t per = c.threads >> c.log_waves;
     const int64_t blocks = ((n + per - 1) / per + 7) / 8 * 8; // a multiple of 8 for the XCD-contiguous remap
     // the blocks' partials go to the sort's second key array, free by now: 16
@@ -859,9 +860,9 @@ void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipS
         at<Header>(ws, L.header), n, self_test ? 1 : 0, c.log_waves, at<V>(ws, L.frep), zpart,
         reinterpret_cast<unsigned long long *>(zpart + blocks));
 }
-template void launch_repulsive<2, float>(int64_t, bool, void *, const Layout &, hipStream_t);
-template void launch_repulsive<2, double>(int64_t, bool, void *, const Layout &, hipStream_t);
-template void launch_repulsive<3, float>(int64_t, bool, void *, const Layout &, hipStream_t);
+template void launch_repulsive<2, float>(int64_t, bool, void *, const Layout &, hipStream_t, int);
+template void launch_repulsive<2, double>(int64_t, bool, void *, const Layout &, hipStream_t, int);
+template void launch_repulsive<3, float>(int64_t, bool, void *, const Layout &, hipStream_t, int);
 
 template <int D, typename T>
 void launch_attract(const int64_t *row_ptr, const int32_t *col, const T *val, int64_t n, int64_t nnz,

@@ -111,7 +111,8 @@ inline bool repulsive_self_test(double theta) { return theta * theta > 0.49; }
 // the same in 3-D: a cube's centre of mass lies within sqrt(3) sides of any of its points
 inline bool repulsive_self_test3(float theta) { return double(theta) * double(theta) > 0.33; }
 template <int D, typename T>
-void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st);
+// form (a test export's; WalkForm): one wave a group by that loop; -1: as n has it
+void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st, int form = -1);
 template <int D, typename T>
 void launch_attract(const int64_t *row_ptr, const int32_t *col, const T *val, int64_t n, int64_t nnz,
                     const StepArgsT<T> &a, T *Y, T *upd, T *gains, T *grad, void *ws, const Layout &L, hipStream_t st);

@@ -120,3 +120,34 @@ def test_box_wider_than_the_largest_float(d):
     P = bh.Csr.from_numpy(np.zeros(5, np.int64), np.zeros(0, np.int32), np.zeros(0, np.float32), device=DEV)
     g, Z = (bh.gradient if d == 2 else bh.gradient_3d)(Y, P, 1e30, 1.0)
     assert Z == 2.0 and not g.any()  # two equal points; everything else weighs 0
+
+
+def _late(n, d, seed):
+    """clusters of very different width, some points repeated"""
+    rng = np.random.default_rng(seed)
+    c = rng.integers(0, 9, n)
+    Y = rng.uniform(-50.0, 50.0, (9, d))[c] + (10.0 ** rng.uniform(-4, 1, 9))[c, None] * rng.normal(size=(n, d))
+    Y[rng.integers(0, n, n // 10)] = Y[0]
+    return Y.astype(np.float32)
+
+
+# Every form of the walk visits the same records for a point and adds them up in the
+# same order: the forces agree bit for bit and the interactions exactly (a wave's list
+# holds 256 entries: theta 0.05 and 0 fill it many times).  Z is summed over other
+# groupings of the points, in fp64.
+@pytest.mark.parametrize("late", [False, True])
+@pytest.mark.parametrize("d, n, theta", [(2, 2, 0.5), (2, 63, 0.8), (2, 65, 0.0), (2, 1025, 0.5), (2, 3001, 0.0),
+                                         (2, 6000, 0.05), (2, 9973, 0.8), (2, 480 * 64, 0.5), (2, 480 * 64 + 1, 0.3),
+                                         (2, 6400 * 64 + 1, 0.5), (3, 3, 0.5), (3, 65, 0.0), (3, 2000, 0.0),
+                                         (3, 2049, 0.8), (3, 128 * 64, 0.2), (3, 128 * 64, 0.5), (3, 128 * 64 + 1, 0.5)])
+def test_walk_forms_agree(d, n, theta, late):
+    Y = _late(n, d, n) if late else (synth.random_y if d == 2 else synth.random_y3)(n, n, dups=n // 10)
+    Y = torch.from_numpy(Y).to(DEV)
+    f, Z, inter = bh.debug_walk(Y, theta)
+    assert torch.isfinite(f).all()
+    if theta == 0.0:
+        assert inter == n * (n - 1)
+    for form in (0, 1) if d == 2 else (1,):
+        f1, Z1, inter1 = bh.debug_walk(Y, theta, form)
+        assert torch.equal(f, f1) and inter == inter1
+        assert abs(Z - Z1) <= 1e-12 * Z
