@@ -332,3 +332,15 @@ def test_3d_layout_size_and_argument_checks():
                                          None) == bh.BHTSNE_EWORKSPACE
     assert lib.bhtsne_step_layout_3d(f, C.byref(l3), 0.5, 1.0, 200.0, 1.0, 0.01, f, f, None, None, f, ws,
                                      None) == bh.BHTSNE_EINVAL
+
+
+@pytest.mark.parametrize("kw", [dict(dim=1), dict(dim=4), dict(form=2), dict(form=-2), dict(dim=3, form=0), dict(n=1),
+                                dict(n=1 << 24), dict(Y=None), dict(frep=None), dict(theta=-1.0),
+                                dict(theta=float("nan"))])
+def test_debug_walk_rejects_bad_arguments(kw):
+    a = dict(Y=FAKE, n=100, dim=2, theta=0.5, form=-1, frep=FAKE)
+    a.update(kw)
+    Z, inter = C.c_double(0.0), C.c_uint64(0)
+    rc = bh.load_library().bhtsne_debug_walk(a["Y"], a["n"], a["dim"], a["theta"], a["form"], a["frep"], C.byref(Z),
+                                             C.byref(inter), FAKE, 1 << 40, None)
+    assert rc == bh.BHTSNE_EINVAL

@@ -25,7 +25,18 @@ def say(*a):
 
 @pytest.mark.parametrize("form", ["layout", "plain", "fp64", "layout3d"])
 def test_step_replays_in_a_graph(form):
-    inp = synth.make_inputs(1, dim=3 if form == "layout3d" else 2)
+    _check_replays(form, synth.make_inputs(1, dim=3 if form == "layout3d" else 2))
+
+
+# the sizes whose places are counted and whose walks share groups (up to 8192 points
+# in 3-D, 30,720 in 2-D fp32), and the first ones past them
+@pytest.mark.parametrize("n", [1500, 8192, 8193, 30_720])
+@pytest.mark.parametrize("form", ["layout", "plain", "fp64", "layout3d"])
+def test_small_step_replays_in_a_graph(form, n):
+    _check_replays(form, synth.make_inputs(1, n=n, dim=3 if form == "layout3d" else 2))
+
+
+def _check_replays(form, inp):
     dev = torch.device(DEV)
     if form == "layout3d":
         Y0 = torch.from_numpy(inp.Y).to(dev)
