@@ -115,7 +115,7 @@ typedef struct bhtsne_stats {
 /* Kernel phases timed by bhtsne_timing_*. */
 enum {
     BHTSNE_PHASE_BBOX_MORTON = 0, /* bounding box + Morton codes */
-    BHTSNE_PHASE_SORT = 1,        /* radix sort of the codes + gather of Y */
+    BHTSNE_PHASE_SORT = 1,        /* sort of the codes + gather of Y */
     BHTSNE_PHASE_TREE = 2,        /* quadtree build + summaries */
     BHTSNE_PHASE_REPULSIVE = 3,   /* Barnes-Hut traversal + Z */
     BHTSNE_PHASE_ATTRACTIVE = 4,  /* attractive forces (plain CSR: with the gradient + update) */

@@ -27,7 +27,7 @@ constexpr int kHistWords = kSortPasses * (1 << kRadixBits);
 constexpr int kSampleStride = 64;
 constexpr int kSamplesPerBucket = 4;
 constexpr int64_t kRankSortMax = 8192;
-constexpr int64_t kSampleSortMax = int64_t(1) << 19; // 2048 buckets, whose splitters fit a block's LDS
+constexpr int64_t kSampleSortMax = int64_t(1) << 19;
 enum class SortMode { kRank, kSample, kRadix };
 inline SortMode sort_mode(int64_t n)
 {
@@ -37,9 +37,7 @@ constexpr int kScanBlock = 256;
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanBlock * kScanItems;
 constexpr int kBBoxBlocks = 512;
-// evaluation kernels: the exact Z takes blocks of kZEvalPoints points, the KL
-// at most kEvalMaxBlocks blocks striding over the rows
-constexpr int kZEvalPoints = 2048;
+// evaluation kernels (exact Z, KL): at most this many blocks, a partial sum each
 constexpr int kEvalMaxBlocks = 2048;
 // repulsive walk: the waves of consecutive points in a block (16 at most) share
 // one CU, so their walks, which overlap in most nodes, share the scalar cache's
@@ -188,8 +186,7 @@ inline Layout make_layout(int64_t n, int64_t nnz, int fbytes = 4, int dim = 2)
     // tiles of kTileRows rows per row block
     L.partial = take(size_t(dim) * size_t(fbytes) * size_t((n + kTileRows - 1) / kTileRows) * kTileRows *
                      size_t(kTileSlots));
-    const int64_t zb = (n + kZEvalPoints - 1) / kZEvalPoints;
-    L.eval_part = take(8 * size_t(zb > kEvalMaxBlocks ? zb : kEvalMaxBlocks));
+    L.eval_part = take(8 * size_t(kEvalMaxBlocks));
     L.total = off;
     return L;
 }

@@ -1,4 +1,4 @@
-// Bounding box, Morton codes and the radix sort of the codes (gfx950).
+// Bounding box, Morton codes and the sort of the codes (gfx950).
 //
 // Quadtree Building (Algorithm 1 and the paragraph on Morton codes): the
 // square domain is centred on the bounding box with half-side r_span, each
@@ -23,7 +23,10 @@
 // with n, and faster.  us of the kernels that make the codes and sort them, by
 // rank / sample / radix: 1500 points 11 / 27 / -, 3000 16 / 33 / 89, 8000 27 / 32 / -,
 // 10k 32 / 31 / 99, 70k - / 48 / 118, 300k - / 124 / 162, 600k - / 227 / 245, 1.3M
-// - / 535 / 430.  The lines lie where they meet.
+// - / 535 / 430.  The first line lies where they meet, the second at the last power of
+// two before they do, near 800k points: whole steps by sample / radix, us, beside the
+// sliced attraction 600k 637 / 661, 700k 702 / 721, 900k 866 / 856, 1.3M 1218 / 1156, beside
+// the windows 600k 934 / 961, 700k 1010 / 1026, 900k 1341 / 1358, 1.3M 2046 / 2013.
 #include "common.hpp"
 #include "kernels.hpp"
 #include <algorithm>
@@ -234,10 +237,10 @@ __device__ inline void add_digits(const uint32_t *sh, uint32_t *__restrict__ his
 // position), and what the sort wants: its samples (kRadixSort = false) or the 8
 // global digit histograms and cleared look-back words of this tile; also clears the
 // per-position tree masks.  Without the radix sort every block finishes the box for
-// itself (2-4 us of a launch for at most 16 KB read again) and takes one point a
-// thread: eight, the radix sort's tile, leave 70k points in 35 blocks.  70k points: the
-// box's last launch and this one took 5.4 + 10.8 us, now 4.8; 1500 points 2.9 + 7.0, now
-// 4.1.
+// itself (2-4 us of a launch for at most 16 KB read again, 32 KB in fp64) and takes
+// one point a thread: eight, the radix sort's tile, leave 70k points in 35 blocks.
+// 70k points: the box's last launch and this one took 5.4 + 10.8 us, now 4.8; 1500
+// points 2.9 + 7.0, now 4.1.
 template <typename T, bool kRadixSort>
 __global__ __launch_bounds__(kSortBlock) void morton_kernel(
     const vec2_t<T> *__restrict__ Y, int64_t n, const T *__restrict__ part, int nparts, Header *__restrict__ hdr,

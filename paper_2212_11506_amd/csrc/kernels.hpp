@@ -84,8 +84,8 @@ template <typename T> void launch_bbox(const T *Y, int64_t n, void *ws, const La
 // Y in the layout's order, ycopy[i] = Y[perm[i]], instead of the caller's
 template <typename T>
 void launch_morton(const T *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L, hipStream_t st);
-// 3-D embeddings (Y n x 3 fp32): box, cube, 63-bit codes, digit histograms and
-// the private copy of Y in the caller's order, or in perm's (nullable) order
+// 3-D embeddings (Y n x 3 fp32): box, cube, 63-bit codes, what the sort
+// wants with them (samples, or digit histograms) and the private copy of Y in the caller's order, or in perm's (nullable) order
 void launch_bbox_morton3(const float *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L,
                          hipStream_t st);
 // ysrc: Y in the original order, gathered into Morton order by the last pass
