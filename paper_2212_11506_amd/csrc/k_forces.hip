@@ -518,9 +518,10 @@ __device__ inline void walk_alone(const char *nbase, uint32_t all, const point_t
 // variant; D = 3: 3-D embeddings (32-byte records).  kForm: one wave walks for a
 // group of 64 points, by the simple loop (2-D fp32, blocks of kRepBlock) or loading
 // ahead, or 2^log_waves waves of a block share the group, each walking a part of
-// the records (in fp32 all waves of the block).  Each is a kernel of its own: with the simple and the load-ahead
-// loop in one kernel, which chose at run time, the simple one's walk took 0.5 to 0.8%
-// longer (700k points 382.2 us, now 378.8; 1M at theta 0.2 1397.7, now 1389.0).
+// the records (in fp32 all waves of the block).  Each is a kernel of its own: with
+// the simple and the load-ahead loop in one kernel, which chose at run time, the
+// simple one's walk took 0.5 to 0.8% longer (700k points 382.2 us, now 378.8; 1M at
+// theta 0.2 1397.7, now 1389.0).
 enum WalkForm { kSimple, kAhead, kShared };
 
 template <int D, typename T, int kForm>

@@ -84,8 +84,9 @@ template <typename T> void launch_bbox(const T *Y, int64_t n, void *ws, const La
 // Y in the layout's order, ycopy[i] = Y[perm[i]], instead of the caller's
 template <typename T>
 void launch_morton(const T *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L, hipStream_t st);
-// 3-D embeddings (Y n x 3 fp32): box, cube, 63-bit codes, what the sort
-// wants with them (samples, or digit histograms) and the private copy of Y in the caller's order, or in perm's (nullable) order
+// 3-D embeddings (Y n x 3 fp32): box, cube, 63-bit codes, what the sort wants
+// with them (samples, or digit histograms) and the private copy of Y in the
+// caller's order, or in perm's (nullable) order
 void launch_bbox_morton3(const float *Y, int64_t n, const uint32_t *perm, void *ws, const Layout &L,
                          hipStream_t st);
 // ysrc: Y in the original order, gathered into Morton order by the last pass
@@ -110,8 +111,8 @@ inline bool repulsive_self_test(float theta) { return double(theta) * double(the
 inline bool repulsive_self_test(double theta) { return theta * theta > 0.49; }
 // the same in 3-D: a cube's centre of mass lies within sqrt(3) sides of any of its points
 inline bool repulsive_self_test3(float theta) { return double(theta) * double(theta) > 0.33; }
-template <int D, typename T>
 // form (a test export's; WalkForm): one wave a group by that loop; -1: as n has it
+template <int D, typename T>
 void launch_repulsive(int64_t n, bool self_test, void *ws, const Layout &L, hipStream_t st, int form = -1);
 template <int D, typename T>
 void launch_attract(const int64_t *row_ptr, const int32_t *col, const T *val, int64_t n, int64_t nnz,

@@ -1,8 +1,9 @@
 """Relabelled rows of a layout at the lengths where their sort changes form (one,
-two, four and eight registers a lane, then LDS, then in their own order), at the
-point count from which eight registers do not serve, with columns out of range and graphs whose components only the later entries of a row join: the
-gradient through the layout against the oracle (rel-L2 1e-3, Z 1e-5) on valid
-rows, and against the plain call (1e-5) where columns are out of range."""
+two, four and eight registers a lane, then LDS, then in their own order), with
+columns out of range and graphs whose components only the later entries of a row
+join: the gradient through the layout against the oracle (rel-L2 1e-3, Z 1e-5) on
+valid rows, and against the plain call (1e-5) where columns are out of range.  At the
+point count from which eight registers do not serve, the rows themselves."""
 from types import SimpleNamespace
 
 import numpy as np
