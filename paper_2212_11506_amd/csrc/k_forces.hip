@@ -98,20 +98,22 @@ __device__ inline void keep_loaded(const u32x8 &r) { asm volatile("" ::"s"(r[5])
 // 622 us, fp64 400k 451 -> 424, 2-D fp32 150k 151 -> 139.  One exit a round: whole
 // steps at 70k points 205 -> 195 us.  With 8 waves a SIMD the 2-D fp32 walk is bound
 // by issue, and the simple loop, which picks the next record last, serves there.)
-template <bool kSelf, bool kAhead>
-__device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi, uint32_t si, uint32_t &resume,
-                                      float &fx, float &fy, float &z, uint32_t &inter)
+//
+// The walk goes from `cur` (a byte offset) to `end`.  kPart: `end` may lie before the
+// last record; the second visit of a round then takes nothing when it is past it.
+template <bool kSelf, bool kAhead, bool kPart = false>
+__device__ inline void repulsive_walk(const char *nbase, uint32_t cur, uint32_t end, float2 yi, uint32_t si,
+                                      uint32_t &resume, float &fx, float &fy, float &z, uint32_t &inter)
 {
-    uint32_t cur = 0; // byte offset of the current record
     if (cur >= end) return;
-    auto visit = [&](const u32x8 &r, u32x8 &after) {
+    auto visit = [&](const u32x8 &r, u32x8 &after, bool live) {
         if (kAhead) keep_loaded(r);
         const float cx = __uint_as_float(r[0]), cy = __uint_as_float(r[1]);
         const float cnt = __uint_as_float(r[2]), thr = __uint_as_float(r[3]);
         const uint32_t next = r[4];
         const float dx = yi.x - cx, dy = yi.y - cy;
         const float d2 = fmaf(dx, dx, dy * dy);
-        const uint64_t act = mask_uge(cur, resume);
+        const uint64_t act = live ? mask_uge(cur, resume) : 0;
         uint64_t take = act & mask_ogt(d2, thr);
         if (kSelf) take &= mask_ne(r[5], si);
         // the first child follows its cell; no lane descends: jump past the subtree
@@ -127,14 +129,14 @@ __device__ inline void repulsive_walk(const char *nbase, uint32_t end, float2 yi
     if (!kAhead) {
         u32x8 none;
         do {
-            visit(load_record(nbase, cur), none);
+            visit(load_record(nbase, cur), none, true);
         } while (cur < end);
         return;
     }
     u32x8 a = load_record(nbase, cur), b;
     do {
-        visit(a, b);
-        visit(b, a);
+        visit(a, b, true);
+        visit(b, a, !kPart || cur < end);
     } while (cur < end);
     keep_loaded(a);
     keep_loaded(b);
@@ -170,20 +172,19 @@ __device__ inline void take_node3(uint64_t take, float d2, float dx, float dy, f
 // accepts a cell containing it (the centre of mass lies in the cell's cube,
 // so the squared distance is at most 3 side^2, below side^2 / theta^2), and
 // the lane's own leaf is taken once with weight 1 as in 2-D.
-template <bool kSelf>
-__device__ inline void repulsive_walk3(const char *nbase, uint32_t end, float3 yi, uint32_t si, uint32_t &resume,
-                                       float &fx, float &fy, float &fz, float &z, uint32_t &inter)
+template <bool kSelf, bool kPart = false>
+__device__ inline void repulsive_walk3(const char *nbase, uint32_t cur, uint32_t end, float3 yi, uint32_t si,
+                                       uint32_t &resume, float &fx, float &fy, float &fz, float &z, uint32_t &inter)
 {
-    uint32_t cur = 0;
     if (cur >= end) return;
-    auto visit = [&](const u32x8 &r, u32x8 &after) {
+    auto visit = [&](const u32x8 &r, u32x8 &after, bool live) {
         keep_loaded(r);
         const float dx = yi.x - __uint_as_float(r[0]), dy = yi.y - __uint_as_float(r[1]);
         const float dz = yi.z - __uint_as_float(r[2]);
         const float cnt = __uint_as_float(r[3]), thr = __uint_as_float(r[4]);
         const uint32_t next = r[5];
         const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        const uint64_t act = mask_uge(cur, resume);
+        const uint64_t act = live ? mask_uge(cur, resume) : 0;
         uint64_t take = act & mask_ogt(d2, thr);
         if (kSelf) take &= mask_ne(r[6], si);
         cur = take != act ? cur + kNodeBytes3 : next;
@@ -194,8 +195,8 @@ __device__ inline void repulsive_walk3(const char *nbase, uint32_t end, float3 y
     };
     u32x8 a = load_record(nbase, cur), b;
     do { // (two visits a round, as in 2-D)
-        visit(a, b);
-        visit(b, a);
+        visit(a, b, true);
+        visit(b, a, !kPart || cur < end);
     } while (cur < end);
     keep_loaded(a);
     keep_loaded(b);
@@ -340,35 +341,38 @@ __device__ inline uint32_t part_bound(uint32_t q, uint32_t parts, uint32_t mid, 
 // later.)  Listing leaves out the reciprocal and the sums, 10 vector instructions
 // a visit instead of 14, and adding up has no chain but the sums.
 constexpr int kListRoom = 256; // entries of a wave's list
-// Half the widest box that waves share.  In a wider one an entry may be infinitely
-// far in fp32 from a lane that does not take it, and counting it 0 times would make
-// the lane's sums NaN; the group's first wave walks alone there.
+// Half the widest box whose entries are listed.  In a wider one an entry may be
+// infinitely far in fp32 from a lane that does not take it, and counting it 0 times
+// would make the lane's sums NaN; the group's first wave walks alone there.
 constexpr double kWidest = 1e38;
 
 struct Lists { // in LDS, `waves` lists of kListRoom entries
     float4 *c;
     uint32_t *lo, *hi;
-    int *len, *done, *part;
-    static size_t bytes(int waves) { return size_t(waves) * (kListRoom * 24 + 8) + 4; }
+    uint32_t *resume, *cur, *end; // where a part's listing stopped
+    int *len;
+    static size_t bytes(int waves) { return size_t(waves) * (kListRoom * 24 + kWave * 4 + 12); }
     __device__ Lists(char *m, int waves)
     {
         c = reinterpret_cast<float4 *>(m);
         lo = reinterpret_cast<uint32_t *>(c + waves * kListRoom);
         hi = lo + waves * kListRoom;
-        len = reinterpret_cast<int *>(hi + waves * kListRoom);
-        done = len + waves;
-        part = done + waves;
+        resume = hi + waves * kListRoom;
+        cur = resume + waves * kWave;
+        end = cur + waves;
+        len = reinterpret_cast<int *>(end + waves);
     }
 };
 
-// Walks on from `cur` until the part ends or the list is full; returns the list's length.
+// Walks on from `cur` until the part ends or the list holds `room` entries (a multiple
+// of 64); returns the list's length.
 template <int D, bool kSelf>
 __device__ inline int walk_list(const char *nbase, uint32_t &cur, uint32_t end, const point_t<D, float> &yi, uint32_t si,
-                                uint32_t &resume, uint32_t &inter, const Lists &l, int first, int len)
+                                uint32_t &resume, uint32_t &inter, const Lists &l, int first, int room)
 {
     constexpr uint32_t kBytes = uint32_t(node_bytes<D, float>());
     uint32_t rec = 0, lo = 0, hi = 0; // the last up to 64 entries, one a lane
-    int fill = 0;
+    int fill = 0, len = 0;
     auto visit = [&](const u32x8 &r, u32x8 &after) {
         keep_loaded(r);
         asm volatile("" ::"s"(r[D])); // (the count)
@@ -406,7 +410,7 @@ __device__ inline int walk_list(const char *nbase, uint32_t &cur, uint32_t end, 
         fill += take != 0 ? 1 : 0;
         return cur < end && fill < kWave;
     };
-    while (cur < end && len + kWave <= kListRoom) {
+    while (cur < end && len + kWave <= room) {
         u32x8 a = load_record(nbase, cur), b = a;
         while (visit(a, b) && visit(b, a)) {
         }
@@ -470,48 +474,39 @@ __device__ inline void add_list(const Lists &l, int first, int len, const point_
     for (; k < len; ++k) add(c[k], mask[k]);
 }
 
-// The walk of a block's waves, which share one group of points.  Where a list fills
-// up before its part ends, the waves meet, the first adds up what comes next in
-// order, and the part whose list that emptied walks on: at least one part ends or
-// empties its list each round, so the rounds end.
+// The walk of a block's waves, which share one group of points: every wave lists its
+// part until it ends or its list is full, then the first adds the lists up in order,
+// and walks what is left of a part itself, from where its listing stopped.  (Before,
+// lists were filled and added up in turns until every part ended, one of the two
+// waiting for the other, which long runs of taken records showed.  Walk in us, one wave
+// a group by the simple loop / in turns / now: 30k points, 27k of them in three places,
+// 1380 / 1622 / 1182; 20k in one place 2973 / 3508 / 2578; 30k at theta 0.05 2473 / 2367
+// / 1659; 3-D 8192 at theta 0.2 1057 / 906 / 636.)
 template <int D, bool kSelf>
 __device__ inline void walk_shared(const char *nbase, uint32_t cur, uint32_t end, const point_t<D, float> &yi,
-                                   uint32_t si, int me, int parts, uint32_t &resume, float &fx, float &fy, float &fz,
-                                   float &z, uint32_t &inter, const Lists &l)
+                                   uint32_t si, int me, int parts, int room, uint32_t &resume, float &fx, float &fy,
+                                   float &fz, float &z, uint32_t &inter, const Lists &l)
 {
-    int len = 0, part = 0; // part: the first one that is not added up yet
-    for (;;) {
-        if (me >= part) len = walk_list<D, kSelf>(nbase, cur, end, yi, si, resume, inter, l, me * kListRoom, len);
-        if (lane_id() == 0) {
-            l.len[me] = len;
-            l.done[me] = cur >= end;
-        }
-        __syncthreads();
-        if (me == 0) {
-            while (part < parts) {
-                add_list<D>(l, part * kListRoom, int(uniform(uint32_t(l.len[part]))), yi, fx, fy, fz, z);
-                if (!uniform(uint32_t(l.done[part]))) break; // its list is empty now
-                ++part;
-            }
-            if (lane_id() == 0) *l.part = part;
-        }
-        __syncthreads();
-        // (read by all before any wave passes the next round's first barrier)
-        part = int(uniform(uint32_t(*l.part)));
-        if (part == parts) return;
-        if (me == part) len = 0;
+    const int len = walk_list<D, kSelf>(nbase, cur, end, yi, si, resume, inter, l, me * kListRoom, room);
+    l.resume[me * kWave + lane_id()] = resume;
+    if (lane_id() == 0) {
+        l.len[me] = len;
+        l.cur[me] = cur;
+        l.end[me] = end;
     }
-}
-
-// One wave's walk over all records, which end at `all`.
-template <int D, bool kSelf>
-__device__ inline void walk_alone(const char *nbase, uint32_t all, const point_t<D, float> &yi, uint32_t si,
-                                  uint32_t &resume, float &fx, float &fy, float &fz, float &z, uint32_t &inter)
-{
-    if constexpr (D == 3)
-        repulsive_walk3<kSelf>(nbase, all, yi, si, resume, fx, fy, fz, z, inter);
-    else
-        repulsive_walk<kSelf, false>(nbase, all, yi, si, resume, fx, fy, z, inter);
+    __syncthreads();
+    if (me != 0) return;
+    for (int p = 0; p < parts; ++p) {
+        add_list<D>(l, p * kListRoom, int(uniform(uint32_t(l.len[p]))), yi, fx, fy, fz, z);
+        cur = uniform(l.cur[p]);
+        end = uniform(l.end[p]);
+        if (cur >= end) continue;
+        resume = l.resume[p * kWave + lane_id()];
+        if constexpr (D == 3)
+            repulsive_walk3<kSelf, true>(nbase, cur, end, yi, si, resume, fx, fy, fz, z, inter);
+        else
+            repulsive_walk<kSelf, true, true>(nbase, cur, end, yi, si, resume, fx, fy, z, inter);
+    }
 }
 
 // D = 2, T = float: the path (24-byte records); T = double: the fp64
@@ -585,25 +580,22 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
     uint32_t inter = 0; // this wave's interactions (a launch has fewer than 2^32 per wave)
     if constexpr (kSplit && sizeof(T) == 4) {
         extern __shared__ float4 s_lists[];
-        const bool wide = uniform(hdr->rspan < kWidest ? 0u : 1u) != 0;
         const Lists lists(reinterpret_cast<char *>(s_lists), waves); // one group a block: me is the wave's number
-        if (wide) {
-            if (me == 0) {
-                if (self_test)
-                    walk_alone<D, true>(nodes, all, yi, si, resume, fx, fy, fz, z, inter);
-                else
-                    walk_alone<D, false>(nodes, all, yi, si, resume, fx, fy, fz, z, inter);
-            }
-        } else if (self_test) {
-            walk_shared<D, true>(nodes, cur, end, yi, si, int(me), waves, resume, fx, fy, fz, z, inter, lists);
-        } else {
-            walk_shared<D, false>(nodes, cur, end, yi, si, int(me), waves, resume, fx, fy, fz, z, inter, lists);
+        int room = kListRoom;
+        if (uniform(hdr->rspan < kWidest ? 0u : 1u)) { // the first wave takes all records
+            room = 0;
+            cur = 0;
+            end = me == 0 ? all : 0;
         }
+        if (self_test)
+            walk_shared<D, true>(nodes, cur, end, yi, si, int(me), waves, room, resume, fx, fy, fz, z, inter, lists);
+        else
+            walk_shared<D, false>(nodes, cur, end, yi, si, int(me), waves, room, resume, fx, fy, fz, z, inter, lists);
     } else if constexpr (D == 3) {
         if (self_test)
-            repulsive_walk3<true>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
+            repulsive_walk3<true>(nodes, cur, end, yi, si, resume, fx, fy, fz, z, inter);
         else
-            repulsive_walk3<false>(nodes, end, yi, si, resume, fx, fy, fz, z, inter);
+            repulsive_walk3<false>(nodes, cur, end, yi, si, resume, fx, fy, fz, z, inter);
     } else if constexpr (sizeof(T) == 8) {
         if (self_test)
             repulsive_walk64<true>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
@@ -611,9 +603,9 @@ __global__ __launch_bounds__(kRepBlock) void repulsive_kernel(
             repulsive_walk64<false>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
     } else {
         if (self_test)
-            repulsive_walk<true, kForm == kAhead>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<true, kForm == kAhead>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
         else
-            repulsive_walk<false, kForm == kAhead>(nodes, end, yi, si, resume, fx, fy, z, inter);
+            repulsive_walk<false, kForm == kAhead>(nodes, cur, end, yi, si, resume, fx, fy, z, inter);
     }
     if constexpr (kSplit) asm volatile("" ::"v"(touched)); // the loads above are wanted, not their values
     bool lead = true; // this wave finishes its group's points
@@ -818,7 +810,7 @@ __global__ __launch_bounds__(256) void attract_kernel(
 //         141, 300k (226) 200, 500k 256; 1024 threads, simple: 500k 235, 1M 447
 //   fp64  5k (203) 41 with 16 waves, 50k (237) 79 with 4, 200k (281) 198 with 2, 400k
 //         (451) 374 with 2; 600k 503 with 1 and 512 threads, 562 with 1024
-//   3-D   5k (328) 181 with 16 waves, 225 with 1; 20k 203 against 208; 1 wave, 256
+//   3-D   5k (328) 168 with 16 waves, 225 with 1; 20k 203 against 208; 1 wave, 256
 //         threads: 50k (397) 299, 150k (718) 539, 300k (930) 664, 800k (1717) 1380 early
 //         and (1371) 1119 late in a run, 1.3M (2503) 2049
 struct WalkLaunch {

@@ -131,18 +131,17 @@ def _late(n, d, seed):
     return Y.astype(np.float32)
 
 
-# Every form of the walk visits the same records for a point and adds them up in the
-# same order: the forces agree bit for bit and the interactions exactly (a wave's list
-# holds 256 entries: theta 0.05 and 0 fill it many times).  Z is summed over other
-# groupings of the points, in fp64.
-@pytest.mark.parametrize("late", [False, True])
-@pytest.mark.parametrize("d, n, theta", [(2, 2, 0.5), (2, 63, 0.8), (2, 65, 0.0), (2, 1025, 0.5), (2, 3001, 0.0),
-                                         (2, 6000, 0.05), (2, 9973, 0.8), (2, 480 * 64, 0.5), (2, 480 * 64 + 1, 0.3),
-                                         (2, 6400 * 64 + 1, 0.5), (3, 3, 0.5), (3, 65, 0.0), (3, 2000, 0.0),
-                                         (3, 2049, 0.8), (3, 128 * 64, 0.2), (3, 128 * 64, 0.5), (3, 128 * 64 + 1, 0.5)])
-def test_walk_forms_agree(d, n, theta, late):
-    Y = _late(n, d, n) if late else (synth.random_y if d == 2 else synth.random_y3)(n, n, dups=n // 10)
-    Y = torch.from_numpy(Y).to(DEV)
+def _buckets(n, d, seed):
+    """nine points in ten in three places"""
+    rng = np.random.default_rng(seed)
+    Y = rng.normal(size=(n, d))
+    m = rng.random(n) < 0.9
+    Y[m] = Y[rng.integers(0, 3, n)][m]
+    return Y.astype(np.float32)
+
+
+def _same_in_every_form(Y, theta):
+    n, d = Y.shape
     f, Z, inter = bh.debug_walk(Y, theta)
     assert torch.isfinite(f).all()
     if theta == 0.0:
@@ -151,3 +150,31 @@ def test_walk_forms_agree(d, n, theta, late):
         f1, Z1, inter1 = bh.debug_walk(Y, theta, form)
         assert torch.equal(f, f1) and inter == inter1
         assert abs(Z - Z1) <= 1e-12 * Z
+
+
+# Every form of the walk visits the same records for a point and adds them up in the
+# same order: the forces agree bit for bit and the interactions exactly (a wave's list
+# holds 256 entries: theta 0.05 and 0 fill it, and what is left of its part is walked).
+# Z is summed over other groupings of the points, in fp64.
+@pytest.mark.parametrize("late", [False, True])
+@pytest.mark.parametrize("d, n, theta", [(2, 2, 0.5), (2, 63, 0.8), (2, 65, 0.0), (2, 1025, 0.5), (2, 3001, 0.0),
+                                         (2, 6000, 0.05), (2, 9973, 0.8), (2, 480 * 64, 0.5), (2, 480 * 64 + 1, 0.3),
+                                         (2, 6400 * 64 + 1, 0.5), (3, 3, 0.5), (3, 65, 0.0), (3, 2000, 0.0),
+                                         (3, 2049, 0.8), (3, 128 * 64, 0.2), (3, 128 * 64, 0.5), (3, 128 * 64 + 1, 0.5)])
+def test_walk_forms_agree(d, n, theta, late):
+    Y = _late(n, d, n) if late else (synth.random_y if d == 2 else synth.random_y3)(n, n, dups=n // 10)
+    Y = torch.from_numpy(Y).to(DEV)
+    _same_in_every_form(Y, theta)
+
+
+# A list filled in the middle of a bucket, whose points are records one behind another:
+# parts with an odd and an even number of them left, and several such parts in a group.
+@pytest.mark.parametrize("theta", [0.1, 0.5, 0.8])
+@pytest.mark.parametrize("d, n", [(2, 700), (2, 701), (2, 5003), (2, 480 * 64), (3, 700), (3, 701), (3, 128 * 64)])
+def test_walk_forms_agree_in_buckets(d, n, theta):
+    _same_in_every_form(torch.from_numpy(_buckets(n, d, n)).to(DEV), theta)
+
+
+@pytest.mark.parametrize("d, n", [(2, 257), (2, 4001), (2, 4002), (3, 4001), (3, 4002)])
+def test_walk_forms_agree_in_one_place(d, n):
+    _same_in_every_form(torch.full((n, d), 1.5, device=DEV), 0.5)
